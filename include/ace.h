@@ -75,8 +75,8 @@ int ace_ctx_set_stream(ace_ctx* ctx, void* hip_stream);
 
 /* 1 if a box edge n is compiled for the given dtype, else 0.  Edges 8, 9, 10, 12, 15, 16, 20,
  * 24, 32, 40, 48, 56 and 64 (padded edges with radices 2, 3, 5, 7) in every dtype; where the
- * padded P x P plane of the XY pass does not fit in LDS (FP64 at 56 and 64) the pass keeps the
- * N y-transformed rows and runs the x transforms over strips of columns. */
+ * padded P x P plane of the XY pass does not fit in LDS (FP64 at 56 and 64) the pass works it in
+ * two halves of its y frequencies. */
 int ace_size_supported(int n, int dtype);
 
 /*

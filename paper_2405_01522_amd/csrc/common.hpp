@@ -154,7 +154,7 @@ __host__ __device__ __forceinline__ T fma_k(T x, double c, T acc) {
     const SplitF k = split_f(c);
     return k.lo == 0.0f ? fmaf(x, k.hi, acc) : fmaf(x, k.hi, fmaf(x, k.lo, acc));
   } else {
-    return acc + x * T(c);
+    return fma(x, T(c), acc);
   }
 }
 
@@ -193,7 +193,7 @@ __host__ __device__ __forceinline__ C2<T> cmul_k(C2<T> a, double c, double s) {
               fmaf(a.r, ks.hi, fmaf(a.i, kc.hi, a.r * ks.lo))};
     }
   }
-  return {a.r * T(c) - a.i * T(s), a.r * T(s) + a.i * T(c)};
+  return {T(fma(a.r, T(c), -a.i * T(s))), T(fma(a.r, T(s), a.i * T(c)))};
 }
 
 // Odd-radix butterfly constants as unit-magnitude float pairs: for each angle 2 pi m / R the
@@ -269,12 +269,13 @@ struct alignas(8) TwE<float> {
   float c, s;
 };
 
-// a * w and a * conj(w) for a table twiddle w
+// a * w and a * conj(w) for a table twiddle w (fma written out: left to the compiler, which of
+// the two products is fused differs from kernel to kernel, and so would the last bit)
 __host__ __device__ __forceinline__ C2<double> tw_mul(C2<double> a, TwE<double> w) {
-  return {a.r * w.c - a.i * w.s, a.r * w.s + a.i * w.c};
+  return {fma(a.r, w.c, -a.i * w.s), fma(a.r, w.s, a.i * w.c)};
 }
 __host__ __device__ __forceinline__ C2<double> tw_mul_conj(C2<double> a, TwE<double> w) {
-  return {a.r * w.c + a.i * w.s, a.i * w.c - a.r * w.s};
+  return {fma(a.r, w.c, a.i * w.s), fma(a.i, w.c, -a.r * w.s)};
 }
 __host__ __device__ __forceinline__ C2<float> tw_mul(C2<float> a, TwE<float> w) {
   return {fmaf(a.r, w.c, -a.i * w.s), fmaf(a.r, w.s, a.i * w.c)};

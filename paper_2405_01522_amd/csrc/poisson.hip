@@ -28,12 +28,11 @@ template <typename T, int N, bool RP, typename R>
 __global__ __launch_bounds__(zf_threads<N>()) void k_zfwd(R res, C2<T>* __restrict__ work,
                                                    const TwE<T>* __restrict__ twg) {
   constexpr int P = 2 * N;
-  C2<T>* buf = lds<T>();
-  const TwE<T>* tw = stage_twiddles<T, P>(buf, (size_t)N * (P + 1), twg);
+  const TwE<T>* tw = stage_twiddles<T, N>(lds<T>(), z_elems<N>(), twg);
   __syncthreads();
   const int p = blockIdx.y;
-  zfwd_plane<T, N, RP, R>(res, p, blockIdx.x, work + (size_t)p * P * N * N, tw, buf,
-                          threadIdx.x, zf_threads<N>());
+  zfwd_plane<T, N, RP, R>(res, p, blockIdx.x, work + (size_t)p * P * N * N, tw,
+                          lds<T>(), threadIdx.x, zf_threads<N>());
 }
 
 // XY pass of one system: workgroup (blockIdx.x, p) takes planes K blockIdx.x .. + K - 1 of
@@ -42,26 +41,24 @@ template <typename T, int N, int K, int NT>
 __global__ __launch_bounds__(NT) void k_xy(C2<T>* __restrict__ work, const T* __restrict__ gpos,
                                            const TwE<T>* __restrict__ twg) {
   constexpr int P = 2 * N;
-  C2<T>* pl = lds<T>();
-  const TwE<T>* tw = stage_twiddles<T, P>(pl, (size_t)K * P * (P + 1), twg);
+  const TwE<T>* tw = stage_twiddles<T, N>(lds<T>(), planes_elems<N>(K), twg);
   __syncthreads();
   const int qz0 = blockIdx.x * K, p = blockIdx.y;
   xy_planes<T, N, K>(work + ((size_t)p * P + qz0) * N * N, (size_t)N * N,
-                     gpos + (size_t)qz0 * P * P, pl, tw, threadIdx.x, NT);
+                     gpos + (size_t)qz0 * P * P, lds<T>(), tw, threadIdx.x, NT);
 }
 
-// XY pass with the rows-and-strips layout (planes larger than the LDS): workgroup (qz, p).
-template <typename T, int N, int NT>
-__global__ __launch_bounds__(NT) void k_xy_strips(C2<T>* __restrict__ work,
-                                                  const T* __restrict__ gpos,
-                                                  const TwE<T>* __restrict__ twg) {
-  constexpr int P = 2 * N, SW = strip_width<T, N>();
-  C2<T>* pl = lds<T>();
-  const TwE<T>* tw = stage_twiddles<T, P>(pl, (size_t)N * (P + 1) + (size_t)P * (SW + 1), twg);
+// XY pass with the plane worked by halves: workgroup (qz, p).
+template <typename T, int N>
+__global__ __launch_bounds__((halves_threads<T, N>()), (halves_waves<T, N>())) void k_xy_halves(
+    C2<T>* __restrict__ work, const T* __restrict__ gpos, const TwE<T>* __restrict__ twg) {
+  constexpr int P = 2 * N;
+  const TwE<T>* tw = stage_twiddles<T, N>(lds<T>(), halves_elems<N>(), twg);
   __syncthreads();
   const int qz = blockIdx.x, p = blockIdx.y;
-  xy_strips<T, N, SW>(work + ((size_t)p * P + qz) * N * N, gpos + (size_t)qz * P * P, pl, tw,
-                      threadIdx.x, NT);
+  xy_halves<T, N, halves_threads<T, N>()>(work + ((size_t)p * P + qz) * N * N,
+                                          gpos + (size_t)qz * P * P, lds<T>(),
+                                          tw, threadIdx.x);
 }
 
 // Z-inverse pass of one launch sequence: workgroup (x, p).
@@ -69,12 +66,11 @@ template <typename T, int N, bool RP, typename R>
 __global__ __launch_bounds__(zi_threads<N>()) void k_zinv(const C2<T>* __restrict__ work, R res,
                                                    const TwE<T>* __restrict__ twg) {
   constexpr int P = 2 * N;
-  C2<T>* buf = lds<T>();
-  const TwE<T>* tw = stage_twiddles<T, P>(buf, (size_t)N * (P + 1), twg);
+  const TwE<T>* tw = stage_twiddles<T, N>(lds<T>(), z_elems<N>(), twg);
   __syncthreads();
   const int p = blockIdx.y;
-  zinv_plane<T, N, RP, R>(work + (size_t)p * P * N * N, res, p, blockIdx.x, tw, buf,
-                          threadIdx.x, zi_threads<N>());
+  zinv_plane<T, N, RP, R>(work + (size_t)p * P * N * N, res, p, blockIdx.x, tw,
+                          lds<T>(), threadIdx.x, zi_threads<N>());
 }
 
 // ---------------------------------------------------------------------------------------
@@ -138,8 +134,7 @@ void run_poisson(bool rp, R res, void* work, const void* ghat, const void* tw, h
   const int np = res.np;
   const int items = rp ? (np + 1) / 2 : np;
   if (items <= 0) return;
-  const size_t lds_z = lds_with_twiddles<T, P>((size_t)N * (P + 1));
-  const size_t lds_xy = lds_with_twiddles<T, P>((size_t)P * (P + 1));
+  const size_t lds_z = z_lds<T, N>();
   C2<T>* w = reinterpret_cast<C2<T>*>(work);
   const TwE<T>* t = reinterpret_cast<const TwE<T>*>(tw);
   const T* gh = reinterpret_cast<const T*>(ghat);
@@ -160,13 +155,13 @@ void run_poisson(bool rp, R res, void* work, const void* ghat, const void* tw, h
   }
   {
     TraceScope ts(tr, TR_XY);
-    if constexpr (fits<T, N>()) {
-      constexpr int nt = xy_threads<T, N>();
-      allow_lds(k_xy<T, N, 1, nt>, lds_xy);
-      k_xy<T, N, 1, nt><<<gxy, nt, lds_xy, s>>>(w, gh, t);
+    if constexpr (by_halves<T, N>()) {
+      allow_lds(k_xy_halves<T, N>, halves_lds<T, N>());
+      k_xy_halves<T, N><<<gxy, halves_threads<T, N>(), halves_lds<T, N>(), s>>>(w, gh, t);
     } else {
-      allow_lds(k_xy_strips<T, N, 512>, strip_lds<T, N>());
-      k_xy_strips<T, N, 512><<<gxy, 512, strip_lds<T, N>(), s>>>(w, gh, t);
+      constexpr int nt = xy_threads<T, N>();
+      allow_lds(k_xy<T, N, 1, nt>, planes_lds<T, N>());
+      k_xy<T, N, 1, nt><<<gxy, nt, planes_lds<T, N>(), s>>>(w, gh, t);
     }
   }
   {
@@ -243,14 +238,14 @@ template <typename T, int N>
 static void xy_edge(int nt, void* work, int count, const void* gpos, const void* tw,
                     hipStream_t s) {
   constexpr int P = 2 * N;
-  const size_t lds = lds_with_twiddles<T, P>((size_t)P * (P + 1));
+  const size_t lds = planes_lds<T, N>();
   dim3 grid(P, count);
   C2<T>* w = reinterpret_cast<C2<T>*>(work);
   const T* g = reinterpret_cast<const T*>(gpos);
   const TwE<T>* t = reinterpret_cast<const TwE<T>*>(tw);
-  if constexpr (!fits<T, N>()) {
-    allow_lds(k_xy_strips<T, N, 512>, strip_lds<T, N>());
-    k_xy_strips<T, N, 512><<<grid, 512, strip_lds<T, N>(), s>>>(w, g, t);
+  if constexpr (by_halves<T, N>()) {
+    allow_lds(k_xy_halves<T, N>, halves_lds<T, N>());
+    k_xy_halves<T, N><<<grid, halves_threads<T, N>(), halves_lds<T, N>(), s>>>(w, g, t);
   } else if (nt == 512) {
     allow_lds(k_xy<T, N, 1, 512>, lds);
     k_xy<T, N, 1, 512><<<grid, 512, lds, s>>>(w, g, t);

@@ -48,24 +48,57 @@ __device__ __forceinline__ C2<T>* lds() {
   return reinterpret_cast<C2<T>*>(ace_smem);
 }
 
-// LDS bytes of `elems` complex values followed by the P table twiddles (16-byte aligned).
+// Table twiddles in LDS, behind the pass's `elems` complex values (those start at LDS address 0,
+// so that their accesses need no base: in front of them the table cost the XY pass 4 %).  A lane that works second-factor
+// index n2 needs exp(-2 pi i n2 k1 / P) for every k1.  Two layouts:
+//   plain  the P entries exp(-2 pi i m / P), read at m = n2 k1;
+//   rows   [n2][k1] (P1 P2 = P entries; rows padded by one entry, which spreads them over the
+//          banks where the lanes of a wavefront hold different n2): one address per item
+//          instead of an index product per k1.
+// Rows take 8 % of the XY pass's vector instructions away at edge 64, where a wavefront of the
+// column phases holds a single n2 (halves form, 68 FP32 transforms: 321 -> 311 us, 18 FP64 ones:
+// 180 -> 177 us).  At the other edges it holds two or three, the row reads wait longer on LDS
+// than the instructions they save, and the plain table is as fast or faster (FP32: edge 56 116
+// against 119 us for 33 transforms, edge 48 58.8 against 59.6 us for 32).
+template <typename T, int N>
+struct TwLds {
+  static constexpr int P = Plan<N>::P, P1 = Plan<N>::P1, P2 = Plan<N>::P2;
+  static constexpr bool rows = P2 == 16;
+  static constexpr int S = P1 + 1;  // entries per row
+  static constexpr size_t bytes =
+      ((rows ? (size_t)P2 * S : (size_t)P) * sizeof(TwE<T>) + 15) / 16 * 16;
+};
+
 template <typename T>
 constexpr size_t tw_offset(size_t elems) {
   return (elems * sizeof(C2<T>) + 15) / 16 * 16;
 }
-template <typename T, int P>
+// LDS bytes of `elems` complex values and the twiddle table.
+template <typename T, int N>
 constexpr size_t lds_with_twiddles(size_t elems) {
-  return tw_offset<T>(elems) + (size_t)P * sizeof(TwE<T>);
+  return tw_offset<T>(elems) + TwLds<T, N>::bytes;
 }
 
-// Copy the P twiddles exp(-2 pi i m / P) into LDS after `elems` complex values.
-template <typename T, int P>
+// Fill the LDS table from the global one (exp(-2 pi i m / P), m < P).
+template <typename T, int N>
 __device__ __forceinline__ const TwE<T>* stage_twiddles(C2<T>* base, size_t elems,
                                                         const TwE<T>* __restrict__ tw) {
+  typedef TwLds<T, N> L;
   TwE<T>* s = reinterpret_cast<TwE<T>*>(reinterpret_cast<unsigned char*>(base) +
                                         tw_offset<T>(elems));
-  for (int m = threadIdx.x; m < P; m += blockDim.x) s[m] = tw[m];
+  for (int m = threadIdx.x; m < L::P; m += blockDim.x) {
+    if constexpr (L::rows)
+      s[m / L::P1 * L::S + m % L::P1] = tw[(m / L::P1) * (m % L::P1)];
+    else
+      s[m] = tw[m];
+  }
   return s;
+}
+
+// exp(-2 pi i n2 k1 / P) from the LDS table
+template <typename T, int N>
+__device__ __forceinline__ TwE<T> tw_at(const TwE<T>* tw, int n2, int k1) {
+  return tw[TwLds<T, N>::rows ? n2 * TwLds<T, N>::S + k1 : n2 * k1];
 }
 
 // ---------------------------------------------------------------------------------------
@@ -158,7 +191,7 @@ struct PairsByPointer {
 // ---------------------------------------------------------------------------------------
 // Z-forward pass body: x-plane x of transform p of the resolver res (its pair density formed
 // on the fly), pruned FFT along z, written transposed into this transform's work volume wp
-// [qz][x][y].  buf: N (P+1) complex values of LDS; tw: the table twiddles in LDS.
+// [qz][x][y].  buf: N (P+1) complex values of LDS; tw: the twiddle table in LDS.
 template <typename T, int N, bool RP, typename R>
 __device__ __forceinline__ void zfwd_plane(const R& res, int p, int x, C2<T>* __restrict__ wp,
                                            const TwE<T>* __restrict__ tw,
@@ -208,7 +241,8 @@ __device__ __forceinline__ void zfwd_plane(const R& res, int p, int x, C2<T>* __
     dft_in_half<T, P1, -1>(v);
     buf[y * RS + n2] = v[0];
 #pragma unroll
-    for (int k1 = 1; k1 < P1; ++k1) buf[y * RS + k1 * P2 + n2] = tw_mul(v[k1], tw[n2 * k1]);
+    for (int k1 = 1; k1 < P1; ++k1)
+      buf[y * RS + k1 * P2 + n2] = tw_mul(v[k1], tw_at<T, N>(tw, n2, k1));
   }
   __syncthreads();
   C2<T>* dst0 = wp + (size_t)x * N;
@@ -227,7 +261,7 @@ __device__ __forceinline__ void zfwd_plane(const R& res, int p, int x, C2<T>* __
 // XY pass body: K consecutive qz planes of one transform, each a whole P x P plane in LDS
 // (plane j at pl + j P (P+1)), worked by nt threads (tid = this thread).  g: the first
 // plane's N x N slice (planes g_stride elements apart), gz: its kernel spectrum in position
-// order [qx][qy] (planes P^2 apart), tw: the table twiddles in LDS.  Every item of a phase
+// order [qx][qy] (planes P^2 apart), tw: the twiddle table in LDS.  Every item of a phase
 // is computed the same way whatever K and nt are, so all launch shapes give the same bits.
 template <typename T, int N, int K>
 __device__ __forceinline__ void xy_planes(C2<T>* __restrict__ g, size_t g_stride,
@@ -255,7 +289,8 @@ __device__ __forceinline__ void xy_planes(C2<T>* __restrict__ g, size_t g_stride
     dft_in_half<T, P1, -1>(v);
     pj[x * RS + n2] = v[0];
 #pragma unroll
-    for (int k1 = 1; k1 < P1; ++k1) pj[x * RS + k1 * P2 + n2] = tw_mul(v[k1], tw[n2 * k1]);
+    for (int k1 = 1; k1 < P1; ++k1)
+      pj[x * RS + k1 * P2 + n2] = tw_mul(v[k1], tw_at<T, N>(tw, n2, k1));
   }
   __syncthreads();
   // 2. y forward, second factor
@@ -282,7 +317,8 @@ __device__ __forceinline__ void xy_planes(C2<T>* __restrict__ g, size_t g_stride
     dft_in_half<T, P1, -1>(v);
     pj[n2 * RS + qy] = v[0];
 #pragma unroll
-    for (int k1 = 1; k1 < P1; ++k1) pj[(k1 * P2 + n2) * RS + qy] = tw_mul(v[k1], tw[n2 * k1]);
+    for (int k1 = 1; k1 < P1; ++k1)
+      pj[(k1 * P2 + n2) * RS + qy] = tw_mul(v[k1], tw_at<T, N>(tw, n2, k1));
   }
   // the kernel spectrum values of this thread's first phase-4 item are requested before the
   // barrier, so that their latency overlaps the wait and the phase's LDS reads
@@ -324,7 +360,8 @@ __device__ __forceinline__ void xy_planes(C2<T>* __restrict__ g, size_t g_stride
     C2<T> v[P1];
     v[0] = pj[n2 * RS + qy];
 #pragma unroll
-    for (int k1 = 1; k1 < P1; ++k1) v[k1] = tw_mul_conj(pj[(k1 * P2 + n2) * RS + qy], tw[n2 * k1]);
+    for (int k1 = 1; k1 < P1; ++k1)
+      v[k1] = tw_mul_conj(pj[(k1 * P2 + n2) * RS + qy], tw_at<T, N>(tw, n2, k1));
     dft_out_half<T, P1, 1>(v);
 #pragma unroll
     for (int n1 = 0; n1 < H1; ++n1) pj[(n1 * P2 + n2) * RS + qy] = v[n1];
@@ -352,7 +389,8 @@ __device__ __forceinline__ void xy_planes(C2<T>* __restrict__ g, size_t g_stride
     C2<T> v[P1];
     v[0] = pj[x * RS + n2];
 #pragma unroll
-    for (int k1 = 1; k1 < P1; ++k1) v[k1] = tw_mul_conj(pj[x * RS + k1 * P2 + n2], tw[n2 * k1]);
+    for (int k1 = 1; k1 < P1; ++k1)
+      v[k1] = tw_mul_conj(pj[x * RS + k1 * P2 + n2], tw_at<T, N>(tw, n2, k1));
     dft_out_half<T, P1, 1>(v);
 #pragma unroll
     for (int n1 = 0; n1 < H1; ++n1) gj[x * N + n1 * P2 + n2] = v[n1];
@@ -385,7 +423,8 @@ __device__ __forceinline__ void zinv_plane(const C2<T>* __restrict__ wp, const R
     C2<T> v[P1];
     v[0] = buf[y * RS + n2];
 #pragma unroll
-    for (int k1 = 1; k1 < P1; ++k1) v[k1] = tw_mul_conj(buf[y * RS + k1 * P2 + n2], tw[n2 * k1]);
+    for (int k1 = 1; k1 < P1; ++k1)
+      v[k1] = tw_mul_conj(buf[y * RS + k1 * P2 + n2], tw_at<T, N>(tw, n2, k1));
     dft_out_half<T, P1, 1>(v);
     const size_t base = ((size_t)x * N + y) * N + n2;
     if constexpr (RP) {
@@ -426,137 +465,214 @@ void allow_lds(K kernel, size_t bytes) {
 
 constexpr size_t kMaxLds = 160 * 1024;
 
+// LDS elements and bytes of the passes: an x-plane of a z pass, K whole P x P planes of the XY
+// pass, or one of its planes by halves (P x N).
+template <int N>
+constexpr size_t z_elems() {
+  return (size_t)N * (2 * N + 1);
+}
+template <int N>
+constexpr size_t planes_elems(int k = 1) {
+  return (size_t)k * (2 * N) * (2 * N + 1);
+}
+template <int N>
+constexpr size_t halves_elems() {
+  return (size_t)(2 * N) * (N + 1);
+}
+template <typename T, int N>
+constexpr size_t z_lds() {
+  return lds_with_twiddles<T, N>(z_elems<N>());
+}
+template <typename T, int N>
+constexpr size_t planes_lds(int k = 1) {
+  return lds_with_twiddles<T, N>(planes_elems<N>(k));
+}
+template <typename T, int N>
+constexpr size_t halves_lds() {
+  return lds_with_twiddles<T, N>(halves_elems<N>());
+}
+
 // the whole P x P plane of the XY pass fits in LDS
 template <typename T, int N>
 constexpr bool fits() {
-  return lds_with_twiddles<T, 2 * N>((size_t)(2 * N) * (2 * N + 1)) <= kMaxLds;
-}
-
-// Otherwise (FP64 at edges 56 and 64) the XY pass keeps only the N y-transformed rows in LDS
-// and runs the x transforms over strips of SW columns: the widest divisor SW <= P/2 of P whose
-// strip fits beside the rows, or 0.
-template <typename T, int N>
-constexpr int strip_width() {
-  constexpr int P = 2 * N;
-  for (int sw = P / 2; sw >= 2; --sw)
-    if (P % sw == 0 &&
-        lds_with_twiddles<T, P>((size_t)N * (P + 1) + (size_t)P * (sw + 1)) <= kMaxLds)
-      return sw;
-  return 0;
-}
-template <typename T, int N>
-constexpr size_t strip_lds() {
-  constexpr int P = 2 * N;
-  return lds_with_twiddles<T, P>((size_t)N * (P + 1) + (size_t)P * (strip_width<T, N>() + 1));
+  return planes_lds<T, N>() <= kMaxLds;
 }
 
 // the pair-Poisson passes are compiled for this edge and precision
 template <typename T, int N>
 constexpr bool supported() {
-  return fits<T, N>() || strip_width<T, N>() > 0;
+  return fits<T, N>() || halves_lds<T, N>() <= kMaxLds;
 }
 
-// XY pass of one qz plane with the rows-and-strips layout: rows x < N of the y transform in
-// LDS R[x][qy] (stride P + 1), then for each strip of SW columns the x transform forward, the
-// kernel multiply and the x transform inverse through a strip buffer S[qx][c] (stride SW + 1),
-// the N kept rows written back to R, then the y inverse.  Every item is computed as in
-// xy_planes, only the x transforms go strip by strip.  g: the plane's N x N slice, gz: its
-// kernel spectrum [qx][qy], pl: R followed by S, tw: table twiddles in LDS.
-template <typename T, int N, int SW>
-__device__ __forceinline__ void xy_strips(C2<T>* __restrict__ g, const T* __restrict__ gz,
+// Whether the one-system XY pass (and the per-edge form of the batch) works its planes by
+// halves, its threads, and the wavefronts per SIMD its registers must allow.  By halves wherever
+// the whole plane leaves one workgroup per CU, whose barriers then stop every wavefront of the
+// CU at once (or does not fit at all); where two or more whole planes fit, halving only adds
+// barriers.  Measured, whole plane -> halves, us per launch of the stated transforms:
+//   FP32  edge 64 (68) 357 -> 311, edge 56 (33) 132 -> 115, edge 48 (32) 58.8 -> 65.6,
+//         edge 40 (64) 72 -> 75;
+//   FP64  edge 48 (32) 119 -> 114, edge 40 (32) 86 -> 77, edge 32 (32) 35.0 -> 41;
+//         edges 64 and 56 (18), against x transforms over strips of 8 and 28 columns beside
+//         the N whole rows: 375 -> 177 and 160 -> 141.
+// Vector instructions now issue in 87 % of the slots at edge 64 in FP32 (78 % before).
+// 512 threads: 256 and 768 are slower (FP32 edge 64: 346 and 421 us) except FP64 at edge 56,
+// where 768 threads take 14 items of each column in whole rounds (153 -> 141 us).
+template <typename T, int N>
+constexpr bool by_halves() {
+  return N >= (sizeof(T) == 4 ? 56 : 40);
+}
+template <typename T, int N>
+constexpr int halves_threads() {
+  return sizeof(T) == 8 && N == 56 ? 768 : 512;
+}
+template <typename T, int N>
+constexpr int halves_waves() {
+  return sizeof(T) == 4 ? (N == 56 ? 6 : 4) : (N <= 48 ? 4 : (N == 56 ? 3 : 2));
+}
+
+// XY pass of one qz plane in two halves of its y frequencies: the positions k1 P2 + k2 with k1
+// even, then those with k1 odd (N columns each).  The even and the odd k1 are the two DFTs that
+// dft_in_half / dft_out_half run separately anyway, so each half is complete by itself up to
+// the last sum of the y inverse (even part + twiddled odd part), for which the even part waits
+// in registers.  Every value is computed as in xy_planes.  LDS holds P x N values instead of
+// P x P, in place: row q, column c = (k1 / 2) P2 + k2 at pl[q (N + 1) + c].
+template <typename T, int N, int NT>
+__device__ __forceinline__ void xy_halves(C2<T>* __restrict__ g, const T* __restrict__ gz,
                                           C2<T>* __restrict__ pl, const TwE<T>* __restrict__ tw,
-                                          int tid, int nt) {
+                                          int tid) {
   typedef Plan<N> PL;
-  constexpr int P = PL::P, P1 = PL::P1, P2 = PL::P2, H1 = PL::H1, RS = P + 1, SS = SW + 1;
-  static_assert(P % SW == 0, "whole strips");
-  C2<T>* R = pl;
-  C2<T>* S = pl + N * RS;
-  // 1. y forward, first factor (rows x < N, input y < N): global -> R
-  for (int it = tid; it < N * P2; it += nt) {
-    const int n2 = it % P2, x = it / P2;
-    C2<T> v[P1];
+  constexpr int P = PL::P, P1 = PL::P1, P2 = PL::P2, H1 = PL::H1, RS = N + 1;
+  constexpr int XS = N % 4 == 0 ? 4 : 1;      // row order of phases 1 and 7, see xy_planes
+  constexpr int IT = (N * P2 + NT - 1) / NT;  // phase-1 / phase-7 items per thread
+  C2<T> even[IT][H1];
 #pragma unroll
-    for (int n1 = 0; n1 < H1; ++n1) v[n1] = g[x * N + n1 * P2 + n2];
-    dft_in_half<T, P1, -1>(v);
-    R[x * RS + n2] = v[0];
+  for (int e = 0; e < 2; ++e) {
+    // 1. y forward, first factor (rows x < N, input y < N), k1 = 2 m + e: global -> LDS
 #pragma unroll
-    for (int k1 = 1; k1 < P1; ++k1) R[x * RS + k1 * P2 + n2] = tw_mul(v[k1], tw[n2 * k1]);
-  }
-  __syncthreads();
-  // 2. y forward, second factor
-  for (int it = tid; it < N * P1; it += nt) {
-    const int x = it % N, k1 = it / N;
-    C2<T> v[P2];
-    C2<T>* row = R + x * RS + k1 * P2;
+    for (int u = 0; u < IT; ++u) {
+      const int it = tid + u * NT;
+      if (N * P2 % NT == 0 || it < N * P2) {
+        const int n2 = it % P2, q = it / P2, x = (q % XS) * (N / XS) + q / XS;
+        C2<T> v[H1];
 #pragma unroll
-    for (int k2 = 0; k2 < P2; ++k2) v[k2] = row[k2];
-    dft<T, P2, -1>(v);
+        for (int n1 = 0; n1 < H1; ++n1) v[n1] = g[x * N + n1 * P2 + n2];
+        if (e == 1) {
 #pragma unroll
-    for (int k2 = 0; k2 < P2; ++k2) row[k2] = v[k2];
-  }
-  __syncthreads();
-  for (int q0 = 0; q0 < P; q0 += SW) {
-    // 3a. x forward, first factor, columns q0 .. q0 + SW - 1: R -> S
-    for (int it = tid; it < SW * P2; it += nt) {
-      const int c = it % SW, n2 = it / SW, qy = q0 + c;
-      C2<T> v[P1];
+          for (int m = 0; m < H1; ++m) v[m] = twk<T, P1, -1>(v[m], m);
+        }
+        dft<T, H1, -1>(v);
 #pragma unroll
-      for (int n1 = 0; n1 < H1; ++n1) v[n1] = R[(n1 * P2 + n2) * RS + qy];
-      dft_in_half<T, P1, -1>(v);
-      S[n2 * SS + c] = v[0];
-#pragma unroll
-      for (int k1 = 1; k1 < P1; ++k1) S[(k1 * P2 + n2) * SS + c] = tw_mul(v[k1], tw[n2 * k1]);
+        for (int m = 0; m < H1; ++m)
+          pl[x * RS + m * P2 + n2] = 2 * m + e == 0 ? v[0] : tw_mul(v[m], tw_at<T, N>(tw, n2, 2 * m + e));
+      }
     }
     __syncthreads();
-    // 3b. x forward second factor, kernel multiply, x inverse first factor
-    for (int it = tid; it < SW * P1; it += nt) {
-      const int c = it % SW, k1 = it / SW, qy = q0 + c;
+    // 2. y forward, second factor
+    for (int it = tid; it < N * H1; it += NT) {
+      const int x = it % N, m = it / N;
       C2<T> v[P2];
+      C2<T>* row = pl + x * RS + m * P2;
 #pragma unroll
-      for (int k2 = 0; k2 < P2; ++k2) v[k2] = S[(k1 * P2 + k2) * SS + c];
+      for (int k2 = 0; k2 < P2; ++k2) v[k2] = row[k2];
       dft<T, P2, -1>(v);
 #pragma unroll
-      for (int k2 = 0; k2 < P2; ++k2) v[k2] = cscale(v[k2], gz[(k1 * P2 + k2) * P + qy]);
+      for (int k2 = 0; k2 < P2; ++k2) row[k2] = v[k2];
+    }
+    __syncthreads();
+    // 3. x forward, first factor (N columns, input x < N)
+    for (int it = tid; it < N * P2; it += NT) {
+      const int c = it % N, n2 = it / N;
+      C2<T> v[P1];
+#pragma unroll
+      for (int n1 = 0; n1 < H1; ++n1) v[n1] = pl[(n1 * P2 + n2) * RS + c];
+      dft_in_half<T, P1, -1>(v);
+      pl[n2 * RS + c] = v[0];
+#pragma unroll
+      for (int k1 = 1; k1 < P1; ++k1)
+        pl[(k1 * P2 + n2) * RS + c] = tw_mul(v[k1], tw_at<T, N>(tw, n2, k1));
+    }
+    // the kernel spectrum of this thread's first phase-4 item, requested before the barrier
+    T gpre[P2];
+    if (NT == N * P1 || tid < N * P1) {
+      const int c = tid % N, k1 = tid / N, qy = (2 * (c / P2) + e) * P2 + c % P2;
+#pragma unroll
+      for (int k2 = 0; k2 < P2; ++k2) gpre[k2] = gz[(k1 * P2 + k2) * P + qy];
+    }
+    __syncthreads();
+    // 4. x forward second factor, kernel multiply, x inverse first factor (in registers)
+    auto column = [&](int it, bool first) {
+      const int c = it % N, k1 = it / N;
+      C2<T> v[P2];
+#pragma unroll
+      for (int k2 = 0; k2 < P2; ++k2) v[k2] = pl[(k1 * P2 + k2) * RS + c];
+      if (!first) {
+        const int qy = (2 * (c / P2) + e) * P2 + c % P2;
+#pragma unroll
+        for (int k2 = 0; k2 < P2; ++k2) gpre[k2] = gz[(k1 * P2 + k2) * P + qy];
+      }
+      dft<T, P2, -1>(v);
+#pragma unroll
+      for (int k2 = 0; k2 < P2; ++k2) v[k2] = cscale(v[k2], gpre[k2]);
       dft<T, P2, 1>(v);
 #pragma unroll
-      for (int k2 = 0; k2 < P2; ++k2) S[(k1 * P2 + k2) * SS + c] = v[k2];
+      for (int k2 = 0; k2 < P2; ++k2) pl[(k1 * P2 + k2) * RS + c] = v[k2];
+    };
+    if constexpr (N * P1 == NT) {
+      column(tid, true);
+    } else {
+      for (int it = tid; it < N * P1; it += NT) column(it, it == tid);
     }
     __syncthreads();
-    // 3c. x inverse, second factor, rows x < N: S -> R
-    for (int it = tid; it < SW * P2; it += nt) {
-      const int c = it % SW, n2 = it / SW, qy = q0 + c;
+    // 5. x inverse, second factor, output x < N only
+    for (int it = tid; it < N * P2; it += NT) {
+      const int c = it % N, n2 = it / N;
       C2<T> v[P1];
-      v[0] = S[n2 * SS + c];
+      v[0] = pl[n2 * RS + c];
 #pragma unroll
-      for (int k1 = 1; k1 < P1; ++k1) v[k1] = tw_mul_conj(S[(k1 * P2 + n2) * SS + c], tw[n2 * k1]);
+      for (int k1 = 1; k1 < P1; ++k1)
+        v[k1] = tw_mul_conj(pl[(k1 * P2 + n2) * RS + c], tw_at<T, N>(tw, n2, k1));
       dft_out_half<T, P1, 1>(v);
 #pragma unroll
-      for (int n1 = 0; n1 < H1; ++n1) R[(n1 * P2 + n2) * RS + qy] = v[n1];
+      for (int n1 = 0; n1 < H1; ++n1) pl[(n1 * P2 + n2) * RS + c] = v[n1];
     }
     __syncthreads();
-  }
-  // 4. y inverse, first factor (rows x < N)
-  for (int it = tid; it < N * P1; it += nt) {
-    const int x = it % N, k1 = it / N;
-    C2<T> v[P2];
-    C2<T>* row = R + x * RS + k1 * P2;
+    // 6. y inverse, first factor (rows x < N)
+    for (int it = tid; it < N * H1; it += NT) {
+      const int x = it % N, m = it / N;
+      C2<T> v[P2];
+      C2<T>* row = pl + x * RS + m * P2;
 #pragma unroll
-    for (int k2 = 0; k2 < P2; ++k2) v[k2] = row[k2];
-    dft<T, P2, 1>(v);
+      for (int k2 = 0; k2 < P2; ++k2) v[k2] = row[k2];
+      dft<T, P2, 1>(v);
 #pragma unroll
-    for (int k2 = 0; k2 < P2; ++k2) row[k2] = v[k2];
-  }
-  __syncthreads();
-  // 5. y inverse, second factor, output y < N: R -> global (in place over the input slice)
-  for (int it = tid; it < N * P2; it += nt) {
-    const int n2 = it % P2, x = it / P2;
-    C2<T> v[P1];
-    v[0] = R[x * RS + n2];
+      for (int k2 = 0; k2 < P2; ++k2) row[k2] = v[k2];
+    }
+    __syncthreads();
+    // 7. y inverse, second factor, output y < N: the even part to registers, then the sum of
+    // both parts to global (in place over the input slice)
 #pragma unroll
-    for (int k1 = 1; k1 < P1; ++k1) v[k1] = tw_mul_conj(R[x * RS + k1 * P2 + n2], tw[n2 * k1]);
-    dft_out_half<T, P1, 1>(v);
+    for (int u = 0; u < IT; ++u) {
+      const int it = tid + u * NT;
+      if (N * P2 % NT == 0 || it < N * P2) {
+        const int n2 = it % P2, q = it / P2, x = (q % XS) * (N / XS) + q / XS;
+        C2<T> v[H1];
 #pragma unroll
-    for (int n1 = 0; n1 < H1; ++n1) g[x * N + n1 * P2 + n2] = v[n1];
+        for (int m = 0; m < H1; ++m) {
+          const C2<T> a = pl[x * RS + m * P2 + n2];
+          v[m] = 2 * m + e == 0 ? a : tw_mul_conj(a, tw_at<T, N>(tw, n2, 2 * m + e));
+        }
+        dft<T, H1, 1>(v);
+        if (e == 0) {
+#pragma unroll
+          for (int m = 0; m < H1; ++m) even[u][m] = v[m];
+        } else {
+#pragma unroll
+          for (int m = 0; m < H1; ++m)
+            g[x * N + m * P2 + n2] = cadd(even[u][m], twk<T, P1, 1>(v[m], m));
+        }
+      }
+    }
+    if (e == 0) __syncthreads();
   }
 }
 

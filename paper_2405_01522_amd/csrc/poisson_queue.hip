@@ -41,41 +41,36 @@ struct JobPairs {
 template <typename T, int N, int K>
 constexpr bool xy_k_fits() {
   return fits<T, N>() && (2 * N) % K == 0 &&
-         lds_with_twiddles<T, 2 * N>((size_t)K * 2 * N * (2 * N + 1)) <= kMaxLds;
+         planes_lds<T, N>(K) <= kMaxLds;
 }
 
 // ---- per-item dispatch on the box edge ---------------------------------------------------
 template <typename T, int N, bool RP>
 __device__ __attribute__((noinline)) void zfwd_item_n(const QJob* jb, int x, C2<T>* buf, int nt) {
-  constexpr int P = 2 * N;
-  const TwE<T>* tw =
-      stage_twiddles<T, P>(buf, (size_t)N * (P + 1), reinterpret_cast<const TwE<T>*>(jb->tw));
+  const TwE<T>* tw = stage_twiddles<T, N>(buf, z_elems<N>(), reinterpret_cast<const TwE<T>*>(jb->tw));
   __syncthreads();
   const JobPairs res{jb, jb->np};
-  zfwd_plane<T, N, RP, JobPairs>(res, 0, x, reinterpret_cast<C2<T>*>(jb->work), tw, buf,
-                                 threadIdx.x, nt);
+  zfwd_plane<T, N, RP, JobPairs>(res, 0, x, reinterpret_cast<C2<T>*>(jb->work), tw,
+                                 buf, threadIdx.x, nt);
 }
 
 template <typename T, int N, bool RP>
 __device__ __attribute__((noinline)) void zinv_item_n(const QJob* jb, int x, C2<T>* buf, int nt) {
-  constexpr int P = 2 * N;
-  const TwE<T>* tw =
-      stage_twiddles<T, P>(buf, (size_t)N * (P + 1), reinterpret_cast<const TwE<T>*>(jb->tw));
+  const TwE<T>* tw = stage_twiddles<T, N>(buf, z_elems<N>(), reinterpret_cast<const TwE<T>*>(jb->tw));
   const JobPairs res{jb, jb->np};
   // the twiddles are first read after the pass's own barrier
-  zinv_plane<T, N, RP, JobPairs>(reinterpret_cast<const C2<T>*>(jb->work), res, 0, x, tw, buf,
-                                 threadIdx.x, nt);
+  zinv_plane<T, N, RP, JobPairs>(reinterpret_cast<const C2<T>*>(jb->work), res, 0, x, tw,
+                                 buf, threadIdx.x, nt);
 }
 
 template <typename T, int N, int K>
 __device__ __attribute__((noinline)) void xy_item_nk(const QJob* jb, int qz0, C2<T>* pl, int nt) {
   constexpr int P = 2 * N;
-  const TwE<T>* tw = stage_twiddles<T, P>(pl, (size_t)K * P * (P + 1),
-                                          reinterpret_cast<const TwE<T>*>(jb->tw));
+  const TwE<T>* tw = stage_twiddles<T, N>(pl, planes_elems<N>(K), reinterpret_cast<const TwE<T>*>(jb->tw));
   __syncthreads();
   xy_planes<T, N, K>(reinterpret_cast<C2<T>*>(jb->work) + (size_t)qz0 * N * N, (size_t)N * N,
-                     reinterpret_cast<const T*>(jb->gpos) + (size_t)qz0 * P * P, pl, tw,
-                     threadIdx.x, nt);
+                     reinterpret_cast<const T*>(jb->gpos) + (size_t)qz0 * P * P,
+                     pl, tw, threadIdx.x, nt);
 }
 
 template <typename T, bool RP>
@@ -102,35 +97,34 @@ __device__ __forceinline__ void zinv_item(const QJob* jb, int x, C2<T>* buf, int
   }
 }
 
-template <typename T, int N>
-__device__ __attribute__((noinline)) void xy_strip_item_n(const QJob* jb, int qz, C2<T>* pl,
-                                                          int nt) {
-  constexpr int P = 2 * N, SW = strip_width<T, N>();
-  const TwE<T>* tw = stage_twiddles<T, P>(pl, (size_t)N * (P + 1) + (size_t)P * (SW + 1),
-                                          reinterpret_cast<const TwE<T>*>(jb->tw));
+// one plane by halves, for the edges whose whole plane does not fit in LDS
+template <typename T, int N, int NT>
+__device__ __attribute__((noinline)) void xy_halves_item_n(const QJob* jb, int qz, C2<T>* pl) {
+  constexpr int P = 2 * N;
+  const TwE<T>* tw = stage_twiddles<T, N>(pl, halves_elems<N>(), reinterpret_cast<const TwE<T>*>(jb->tw));
   __syncthreads();
-  xy_strips<T, N, SW>(reinterpret_cast<C2<T>*>(jb->work) + (size_t)qz * N * N,
-                      reinterpret_cast<const T*>(jb->gpos) + (size_t)qz * P * P, pl, tw,
-                      threadIdx.x, nt);
+  xy_halves<T, N, NT>(reinterpret_cast<C2<T>*>(jb->work) + (size_t)qz * N * N,
+                      reinterpret_cast<const T*>(jb->gpos) + (size_t)qz * P * P,
+                      pl, tw, threadIdx.x);
 }
 
-template <typename T>
-__device__ __forceinline__ void xy_item(const QJob* jb, int qz0, C2<T>* pl, int nt) {
+template <typename T, int NT>
+__device__ __forceinline__ void xy_item(const QJob* jb, int qz0, C2<T>* pl) {
   const int k = jb->k;
   switch (jb->edge) {
 #define ACE_CASE(NN)                                                                       \
   case NN:                                                                                 \
     if constexpr (!fits<T, NN>() && supported<T, NN>()) {                                  \
-      xy_strip_item_n<T, NN>(jb, qz0, pl, nt);                                            \
+      xy_halves_item_n<T, NN, NT>(jb, qz0, pl);                                           \
     }                                                                                      \
     if constexpr (xy_k_fits<T, NN, 1>()) {                                                 \
-      if (k == 1) xy_item_nk<T, NN, 1>(jb, qz0, pl, nt);                                  \
+      if (k == 1) xy_item_nk<T, NN, 1>(jb, qz0, pl, NT);                                  \
     }                                                                                      \
     if constexpr (xy_k_fits<T, NN, 2>()) {                                                 \
-      if (k == 2) xy_item_nk<T, NN, 2>(jb, qz0, pl, nt);                                  \
+      if (k == 2) xy_item_nk<T, NN, 2>(jb, qz0, pl, NT);                                  \
     }                                                                                      \
     if constexpr (xy_k_fits<T, NN, 4>()) {                                                 \
-      if (k == 4) xy_item_nk<T, NN, 4>(jb, qz0, pl, nt);                                  \
+      if (k == 4) xy_item_nk<T, NN, 4>(jb, qz0, pl, NT);                                  \
     }                                                                                      \
     break;
     ACE_SIZES(ACE_CASE)
@@ -169,34 +163,27 @@ __global__ __launch_bounds__(NT) void k_zinv_q(const QJob* __restrict__ jobs,
 // occupancy instead of that of a workgroup sized for the largest edge; same bodies, same bits.
 template <typename T, int N, bool RP>
 __global__ __launch_bounds__(zf_threads<N>()) void k_zfwd_e(const QJob* __restrict__ jobs) {
-  constexpr int P = 2 * N;
   const QJob* jb = jobs + blockIdx.y;
-  C2<T>* buf = lds<T>();
-  const TwE<T>* tw =
-      stage_twiddles<T, P>(buf, (size_t)N * (P + 1), reinterpret_cast<const TwE<T>*>(jb->tw));
+  const TwE<T>* tw = stage_twiddles<T, N>(lds<T>(), z_elems<N>(), reinterpret_cast<const TwE<T>*>(jb->tw));
   __syncthreads();
   const JobPairs res{jb, jb->np};
   zfwd_plane<T, N, RP, JobPairs>(res, 0, blockIdx.x, reinterpret_cast<C2<T>*>(jb->work), tw,
-                                 buf, threadIdx.x, zf_threads<N>());
+                                 lds<T>(), threadIdx.x, zf_threads<N>());
 }
 
 template <typename T, int N, bool RP>
 __global__ __launch_bounds__(zi_threads<N>()) void k_zinv_e(const QJob* __restrict__ jobs) {
-  constexpr int P = 2 * N;
   const QJob* jb = jobs + blockIdx.y;
-  C2<T>* buf = lds<T>();
-  const TwE<T>* tw =
-      stage_twiddles<T, P>(buf, (size_t)N * (P + 1), reinterpret_cast<const TwE<T>*>(jb->tw));
+  const TwE<T>* tw = stage_twiddles<T, N>(lds<T>(), z_elems<N>(), reinterpret_cast<const TwE<T>*>(jb->tw));
   const JobPairs res{jb, jb->np};
   // the twiddles are first read after the pass's own barrier
   zinv_plane<T, N, RP, JobPairs>(reinterpret_cast<const C2<T>*>(jb->work), res, 0, blockIdx.x,
-                                 tw, buf, threadIdx.x, zi_threads<N>());
+                                 tw, lds<T>(), threadIdx.x, zi_threads<N>());
 }
 
 template <typename T, int N, bool RP>
 void z_edge(bool forward, const QJob* jobs, int count, hipStream_t s) {
-  constexpr int P = 2 * N;
-  const size_t lds = lds_with_twiddles<T, P>((size_t)N * (P + 1));
+  const size_t lds = z_lds<T, N>();
   dim3 grid(N, count);
   if (forward) {
     allow_lds(k_zfwd_e<T, N, RP>, lds);
@@ -236,7 +223,7 @@ __global__ __launch_bounds__(kXyQueueThreads) void k_xy_q(const QJob* __restrict
   for (int i = blockIdx.x; i < nitems; i += gridDim.x) {
     const QItem it = items[i];
     __syncthreads();
-    xy_item<T>(jobs + it.job, it.idx, pl, kXyQueueThreads);
+    xy_item<T, kXyQueueThreads>(jobs + it.job, it.idx, pl);
   }
 }
 
@@ -303,8 +290,7 @@ size_t xy_lds(int n, int k) {
   switch (n) {
 #define ACE_CASE(NN)                                                                        \
   case NN:                                                                                  \
-    return fits<T, NN>() ? lds_with_twiddles<T, 2 * NN>((size_t)k * 2 * NN * (2 * NN + 1)) \
-                         : strip_lds<T, NN>();
+    return fits<T, NN>() ? planes_lds<T, NN>(k) : halves_lds<T, NN>();
     ACE_SIZES(ACE_CASE)
 #undef ACE_CASE
   }
@@ -318,8 +304,14 @@ bool queue_xy_k_ok(int n, bool fp64, int k) { return fp64 ? k_ok<double>(n, k) :
 size_t queue_xy_lds(int n, bool fp64, int k) { return fp64 ? xy_lds<double>(n, k) : xy_lds<float>(n, k); }
 
 size_t queue_z_lds(int n, bool fp64) {
-  const size_t p = 2 * (size_t)n, e = fp64 ? 16 : 8;
-  return ((size_t)n * (p + 1) * e + 15) / 16 * 16 + p * 16;
+  switch (n) {
+#define ACE_CASE(NN) \
+  case NN:           \
+    return fp64 ? z_lds<double, NN>() : z_lds<float, NN>();
+    ACE_SIZES(ACE_CASE)
+#undef ACE_CASE
+  }
+  return 0;
 }
 
 int launch_zfwd_queue(bool fp64, bool rp, const QJob* jobs, const QItem* zitems, int nz,
