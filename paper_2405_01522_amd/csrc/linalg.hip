@@ -63,12 +63,26 @@ __global__ __launch_bounds__(256) void k_dgemm(int ta, int tb, int M, int N, int
 }
 
 // Symmetric eigendecomposition by the cyclic Jacobi method in round-robin (tournament)
-// order: each round rotates n/2 disjoint index pairs at once.  The rotations of a round are
-// computed once (one thread per pair); the two-sided update is then one pass over 2x2 blocks:
-// the block (rows of pair k, columns of pair l) becomes R_k B R_l^T with R = [[c, -s], [s, c]],
-// and the eigenvector columns of each pair rotate.  One workgroup; matrix and eigenvectors in
-// LDS.  Output: w ascending, V[i][k] = component i of eigenvector k (row-major, leading
-// dimension ldv).
+// order: each round rotates n/2 disjoint index pairs (p < q) at once.  The two-sided update is one
+// pass over 2x2 blocks: the block (rows of pair k, columns of pair l) becomes R_k B R_l^T with
+// R = [[c, -s], [s, c]], and the eigenvector columns of each pair rotate.  One workgroup.
+// Output: w ascending, V[i][k] = component i of eigenvector k (row-major, leading dimension ldv).
+//
+// Rows and columns are held by slots: pair k of the round has slots k (its p) and n/2 + k (its q).
+// What a round writes goes to the slots of the next, by a table made once, so that the blocks'
+// addresses stay the same from round to round.  Bound by the chain of a round (LDS, the rotation's
+// roots and reciprocals with n/2 lanes busy, LDS, barrier) up to n of about 32, by the LDS traffic
+// of A and V beyond, so one barrier per round:
+//  - one wavefront forms the rotations of round t + 1 while round t is applied, from the entries
+//    that round t leaves there (their 2x2 blocks rotated once more for itself, to the same bits);
+//  - the others apply round t to the blocks of A and to V, held by columns, two components to a
+//    thread.
+// Every value is rounded as in the plain form (A by index, the rotations between two barriers), so
+// results are the same to the bit.
+// n = 4 / 16 / 32 / 48 / 60 / 64 (random, to 1e-11): 12 / 54 / 130 / 285 / 400 / 490 us, plain form
+// 18 / 84 / 195 / 432 / 583 / 702 us.  Keeping only the blocks with k <= l and two roots in the
+// rotation came to 228 us at n = 48, but rounds otherwise, and the FP32 block eigensolver behind it
+// turns last bits into 4e-7 of its eigenvalues.
 constexpr int JMAX = 64;
 constexpr int JT = 1024;
 
@@ -86,145 +100,194 @@ __device__ __forceinline__ double rsq_nr(double x) {
   return r;
 }
 
+// Rotation (c, s) that annihilates a_pq:
+// t = sign(theta) / (|theta| + sqrt(theta^2 + 1)), c = 1 / sqrt(t^2 + 1), s = t c;
+// hardware reciprocal / reciprocal square root refined by two Newton steps each (full FP64
+// accuracy, much shorter dependency chains than IEEE division)
+__device__ __forceinline__ double2 rotation(double app, double aqq, double apq) {
+  const bool some = fabs(apq) > 1e-290;  // below that the rotation is the identity to rounding
+  const double theta = (aqq - app) * rcp_nr(2.0 * apq);
+  const double at = fabs(theta);
+  const double r2 = fma(theta, theta, 1.0);
+  double t = (theta >= 0.0 ? 1.0 : -1.0) * rcp_nr(fma(r2, rsq_nr(r2), at));
+  if (some && at > 1e150) t = 0.5 / theta;
+  const double c = rsq_nr(fma(t, t, 1.0));
+  return make_double2(some ? c : 1.0, some ? t * c : 0.0);
+}
+
+// Wavefronts: one for the rotations, jacobi_aw(h) for A, jacobi_vw(h) for V (h = order / 2); the
+// items of a thread: JKA blocks, JKV pieces of V.
+constexpr int JAW = 9, JVW = 6, JKA = 2, JKV = 3;
+__host__ __device__ constexpr int jacobi_aw(int h) {
+  const int v = (h * h + 63) / 64;
+  return v < JAW ? v : JAW;
+}
+__host__ __device__ constexpr int jacobi_vw(int h) {
+  const int v = (h * h + 63) / 64;
+  return v < JVW ? v : JVW;
+}
+static_assert(64 * JAW * JKA >= JMAX / 2 * (JMAX / 2) && 64 * JVW * JKV >= JMAX / 2 * (JMAX / 2) &&
+              64 * (1 + JAW + JVW) <= JT);
+
 __global__ __launch_bounds__(JT) void k_jacobi(int n, const double* __restrict__ Ain, int lda,
                                                double* __restrict__ w, double* __restrict__ V,
                                                int ldv, int max_sweeps, double tol,
                                                const int* __restrict__ skip) {
   if (skip != nullptr && *skip) return;  // the caller's result is already in place
-  __shared__ double a[JMAX][JMAX + 1];
-  __shared__ double v[JMAX][JMAX + 1];
-  __shared__ double cs[JMAX / 2], sn[JMAX / 2];
-  __shared__ int pp[JMAX / 2], qq[JMAX / 2];
+  constexpr int H = JMAX / 2;
+  __shared__ double a2[2][JMAX * JMAX];  // [slot][slot], ld to a row
+  __shared__ double2 v2[2][JMAX * H];    // [slot][component / 2], h to a row
+  __shared__ double2 cf[2][2 * H];       // row of a rotation for a slot: (c, -s) or (s, c)
+  __shared__ unsigned short to[JMAX * H], from[JMAX * H];  // [round][pair], two slots each
   __shared__ double red[2][JT / 64];
   __shared__ int rank_s[JMAX];
   const int m = n + (n & 1);  // even order; a padding index acts as an isolated zero row
-  const int h = m / 2;
-  for (int e = threadIdx.x; e < m * m; e += JT) {
-    const int i = e / m, j = e % m;
+  const int h = m / 2, ld = h + H;  // (rows of blocks follow each other in the LDS banks)
+  const int naw = jacobi_aw(h), nvw = jacobi_vw(h), nt = blockDim.x;
+  // Index at a position in a round: the one at position 0 stays, the others move on by one each
+  // round; positions k and m - 1 - k are pair k.  And the slot of an index in a round.
+  auto index_at = [&](int pos, int t) { return pos == 0 ? 0 : 1 + (pos - 1 + t) % (m - 1); };
+  auto slot_of = [&](int i, int t) {
+    const int pos = i == 0 ? 0 : 1 + (i - 1 + 2 * (m - 1) - t) % (m - 1);
+    return (pos < h ? pos : m - 1 - pos) + (i > index_at(m - 1 - pos, t) ? h : 0);
+  };
+  for (int e = threadIdx.x; e < (m - 1) * h; e += nt) {
+    const int t = e / h, k = e % h;
+    int x = index_at(k, t), y = index_at(m - 1 - k, t);
+    to[e] = slot_of(min(x, y), t + 1) | slot_of(max(x, y), t + 1) << 8;
+    x = index_at(k, t + 1), y = index_at(m - 1 - k, t + 1);
+    from[e] = slot_of(min(x, y), t) | slot_of(max(x, y), t) << 8;
+  }
+  auto slot0 = [&](int i) { return i < h ? i : h + m - 1 - i; };  // slot_of(i, 0)
+  for (int e = threadIdx.x; e < m * JMAX; e += nt) {
+    const int i = e / JMAX, j = e % JMAX;
     double x = 0.0;
     if (i < n && j < n) x = 0.5 * (Ain[(size_t)i * lda + j] + Ain[(size_t)j * lda + i]);
-    a[i][j] = x;
-    v[i][j] = (i == j) ? 1.0 : 0.0;
+    if (j < m) a2[0][slot0(i) * ld + slot0(j)] = x;
+    if (j < h)
+      v2[0][slot0(i) * h + j] = make_double2(2 * j == i ? 1.0 : 0.0, 2 * j + 1 == i ? 1.0 : 0.0);
   }
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool rot = wave == 0, on_a = wave >= 1 && wave <= naw, on_v = wave > naw;
+  const int ta = (int)threadIdx.x - 64, tv = ta - 64 * naw, tr = min((int)threadIdx.x, h - 1);
+  int ak[JKA], al[JKA], vl[JKV], vi[JKV];  // blocks (k, l) and pieces (pair, components / 2)
+#pragma unroll
+  for (int u = 0; u < JKA; ++u) {
+    ak[u] = (ta + u * 64 * naw) / h;
+    al[u] = (ta + u * 64 * naw) % h;
+  }
+#pragma unroll
+  for (int u = 0; u < JKV; ++u) {
+    vl[u] = (tv + u * 64 * nvw) / h;
+    vi[u] = (tv + u * 64 * nvw) % h;
+  }
+  auto put = [&](int half, double2 r) {
+    if ((int)threadIdx.x < h) {
+      cf[half][threadIdx.x] = make_double2(r.x, -r.y);
+      cf[half][h + threadIdx.x] = make_double2(r.y, r.x);
+    }
+  };
   __syncthreads();
+  if (rot) {
+    put(0, rotation(a2[0][tr * ld + tr], a2[0][(h + tr) * (ld + 1)], a2[0][tr * ld + h + tr]));
+    __builtin_amdgcn_s_setprio(3);  // the others wait for it
+  }
+  int cur = 0;                   // the half of a2, v2 and cf in use
+  int next_from = from[tr];  // read one round ahead
   for (int sweep = 0; sweep < max_sweeps; ++sweep) {
     double off = 0.0, tot = 0.0;
-    for (int e = threadIdx.x; e < m * m; e += JT) {
-      const int i = e / m, j = e % m;
-      const double x = a[i][j] * a[i][j];
+    for (int e = threadIdx.x; e < m * JMAX; e += nt) {
+      const int i = e / JMAX, j = e % JMAX;
+      const double x = j < m ? a2[cur][i * ld + j] * a2[cur][i * ld + j] : 0.0;
       tot += x;
       if (i != j) off += x;
     }
-    // wavefront butterflies, then the JT / 64 wavefront sums in order (every thread)
+    // wavefront butterflies, then the wavefronts' sums in order (every thread)
     for (int o = 32; o > 0; o >>= 1) {
       off += __shfl_xor(off, o, 64);
       tot += __shfl_xor(tot, o, 64);
     }
     if ((threadIdx.x & 63) == 0) {
-      red[0][threadIdx.x >> 6] = off;
-      red[1][threadIdx.x >> 6] = tot;
+      red[0][wave] = off;
+      red[1][wave] = tot;
     }
     __syncthreads();
     double offn = 0.0, totn = 0.0;
-    for (int w = 0; w < JT / 64; ++w) {
-      offn += red[0][w];
-      totn += red[1][w];
+    for (int x = 0; x < nt / 64; ++x) {
+      offn += red[0][x];
+      totn += red[1][x];
     }
     __syncthreads();
     if (offn <= tol * tol * totn || offn == 0.0) break;
-    // tournament pairing: position 0 fixed, the others rotate by one each round.  Every thread
-    // keeps the indices at the positions of its work items in registers and advances them
-    // (no LDS reads, no divisions); at round 0 the index at position pos is pos.
-    constexpr int KI = (JMAX / 2 * JMAX / 2 + JMAX * JMAX / 2 + JT - 1) / JT;  // items per thread
-    const int nitem = h * h + m * h;
-    int ia[KI][4];  // A items: positions k, m-1-k, l, m-1-l; V items: l, m-1-l
-#pragma unroll
-    for (int u = 0; u < KI; ++u) {
-      const int e = threadIdx.x + u * JT;
-      const int k = e < h * h ? e / h : (e - h * h) / m;
-      const int l = e < h * h ? e % h : 0;
-      ia[u][0] = k;
-      ia[u][1] = m - 1 - k;
-      ia[u][2] = l;
-      ia[u][3] = m - 1 - l;
-    }
-    int ra = (int)threadIdx.x, rb = m - 1 - (int)threadIdx.x;  // rotation phase (thread < h)
-    auto adv = [&](int x) { return x == 0 ? 0 : (x == m - 1 ? 1 : x + 1); };
     for (int round = 0; round < m - 1; ++round) {
-      if ((int)threadIdx.x < h) {
-        const int k = threadIdx.x;
-        const int p = ra < rb ? ra : rb, q = ra < rb ? rb : ra;
-        const double apq = a[p][q];
-        double c = 1.0, sv = 0.0;
-        if (fabs(apq) > 1e-290) {  // below that the rotation is the identity to rounding
-          // t = sign(theta) / (|theta| + sqrt(theta^2 + 1)), c = 1 / sqrt(t^2 + 1), s = t c;
-          // hardware reciprocal / reciprocal square root refined by two Newton steps each
-          // (full FP64 accuracy, much shorter dependency chains than IEEE division)
-          const double theta = (a[q][q] - a[p][p]) * rcp_nr(2.0 * apq);
-          const double at = fabs(theta);
-          double t;
-          if (at > 1e150) {
-            t = 0.5 / theta;
-          } else {
-            const double r2 = theta * theta + 1.0;
-            t = (theta >= 0.0 ? 1.0 : -1.0) * rcp_nr(at + r2 * rsq_nr(r2));
-          }
-          c = rsq_nr(t * t + 1.0);
-          sv = t * c;
-        }
-        cs[k] = c;
-        sn[k] = sv;
-        ra = adv(ra);
-        rb = adv(rb);
-      }
-      __syncthreads();
-      // A <- J^T A J by 2x2 blocks; V <- V J by column pairs
+      const double* A = a2[cur];
+      double* An = a2[cur ^ 1];
+      if (rot) {  // the next round's rotations, from this round's matrix and rotations
+        const int P = next_from & 255, Q = next_from >> 8;
+        const double2 rp = cf[cur][P], rq = cf[cur][Q];
+        const int X = P < h ? P : P - h, Y = Q < h ? Q : Q - h;
+        double b[3][4];
 #pragma unroll
-      for (int u = 0; u < KI; ++u) {
-        const int e = threadIdx.x + u * JT;
-        if (e < nitem) {
-          const int a0 = ia[u][0], b0 = ia[u][1];
-          const int p = a0 < b0 ? a0 : b0, q = a0 < b0 ? b0 : a0;
-          if (e < h * h) {
-            const int k = e / h, l = e % h;
-            const int a1 = ia[u][2], b1 = ia[u][3];
-            const int r = a1 < b1 ? a1 : b1, t = a1 < b1 ? b1 : a1;
-            const double ck = cs[k], sk = sn[k], cl = cs[l], sl = sn[l];
-            const double b00 = a[p][r], b01 = a[p][t], b10 = a[q][r], b11 = a[q][t];
-            const double r00 = ck * b00 - sk * b10, r01 = ck * b01 - sk * b11;
-            const double r10 = sk * b00 + ck * b10, r11 = sk * b01 + ck * b11;
-            a[p][r] = cl * r00 - sl * r01;
-            a[p][t] = sl * r00 + cl * r01;
-            a[q][r] = cl * r10 - sl * r11;
-            a[q][t] = sl * r10 + cl * r11;
-          } else {
-            const int f = e - h * h;
-            const int l = f / m, i = f % m;
-            const double c = cs[l], sv = sn[l];
-            const double vx = v[i][p], vy = v[i][q];
-            v[i][p] = c * vx - sv * vy;
-            v[i][q] = sv * vx + c * vy;
-          }
+        for (int i = 0; i < 3; ++i) {
+          const double* x = A + (i < 2 ? X : Y) * ld + (i < 1 ? X : Y);
+          b[i][0] = x[0], b[i][1] = x[h], b[i][2] = x[h * ld], b[i][3] = x[h * ld + h];
         }
+        next_from = from[(round + 2 < m ? round + 1 : 0) * h + tr];
+        auto entry = [](const double (&e)[4], double2 rr, double2 rt) {
+          const double r0 = fma(rr.x, e[0], rr.y * e[2]), r1 = fma(rr.x, e[1], rr.y * e[3]);
+          return fma(rt.x, r0, rt.y * r1);
+        };
+        put(cur ^ 1, rotation(entry(b[0], rp, rp), entry(b[2], rq, rq), entry(b[1], rp, rq)));
+      } else if (on_a) {  // A <- J^T A J by 2x2 blocks
 #pragma unroll
-        for (int j = 0; j < 4; ++j) ia[u][j] = adv(ia[u][j]);
+        for (int u = 0; u < JKA; ++u)
+          if (ak[u] < h) {
+            const int tk = to[round * h + ak[u]], tl = to[round * h + al[u]];
+            const double2 k0 = cf[cur][ak[u]], l0 = cf[cur][al[u]];  // (c, -s)
+            const double* b = A + ak[u] * ld + al[u];
+            const double b00 = b[0], b01 = b[h], b10 = b[h * ld], b11 = b[h * ld + h];
+            const double r00 = fma(k0.x, b00, k0.y * b10), r01 = fma(k0.x, b01, k0.y * b11);
+            const double r10 = fma(-k0.y, b00, k0.x * b10), r11 = fma(-k0.y, b01, k0.x * b11);
+            double *const w0 = An + (tk & 255) * ld, *const w1 = An + (tk >> 8) * ld;
+            w0[tl & 255] = fma(l0.x, r00, l0.y * r01);
+            w0[tl >> 8] = fma(-l0.y, r00, l0.x * r01);
+            w1[tl & 255] = fma(l0.x, r10, l0.y * r11);
+            w1[tl >> 8] = fma(-l0.y, r10, l0.x * r11);
+          }
+      } else if (on_v) {  // V <- V J by column pairs
+#pragma unroll
+        for (int u = 0; u < JKV; ++u)
+          if (vl[u] < h) {
+            const int tl = to[round * h + vl[u]];
+            const double2 r = cf[cur][vl[u]];  // (c, -s)
+            const double2 x = v2[cur][vl[u] * h + vi[u]], y = v2[cur][(h + vl[u]) * h + vi[u]];
+            v2[cur ^ 1][(tl & 255) * h + vi[u]] =
+                make_double2(fma(r.x, x.x, r.y * y.x), fma(r.x, x.y, r.y * y.y));
+            v2[cur ^ 1][(tl >> 8) * h + vi[u]] =
+                make_double2(fma(-r.y, x.x, r.x * y.x), fma(-r.y, x.y, r.x * y.y));
+          }
       }
+      cur ^= 1;
       __syncthreads();
     }
   }
+  if (rot) __builtin_amdgcn_s_setprio(0);
   // ascending order: rank of each eigenvalue (ties broken by index)
-  for (int i = threadIdx.x; i < n; i += JT) {
+  const double* a = a2[cur];
+  auto diag = [&](int i) { return a[slot0(i) * (ld + 1)]; };
+  for (int i = threadIdx.x; i < n; i += nt) {
     int r = 0;
     for (int j = 0; j < n; ++j)
-      if (a[j][j] < a[i][i] || (a[j][j] == a[i][i] && j < i)) ++r;
+      if (diag(j) < diag(i) || (diag(j) == diag(i) && j < i)) ++r;
     rank_s[i] = r;
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < n * n; e += JT) {
+  for (int e = threadIdx.x; e < n * n; e += nt) {
     const int i = e / n, k = e % n;  // component i of eigenvector k (unsorted)
-    V[(size_t)i * ldv + rank_s[k]] = v[i][k];
+    const double2 x = v2[cur][slot0(k) * h + (i >> 1)];
+    V[(size_t)i * ldv + rank_s[k]] = i & 1 ? x.y : x.x;
   }
-  for (int k = threadIdx.x; k < n; k += JT) w[rank_s[k]] = a[k][k];
+  for (int k = threadIdx.x; k < n; k += nt) w[rank_s[k]] = diag(k);
 }
 
 // Orthonormalisation of a basis from its Gram matrix S (n <= JMAX, symmetrised on load) by
@@ -475,7 +538,8 @@ void launch_dgemm(int ta, int tb, int M, int N, int K, double alpha, const doubl
 
 void launch_jacobi(int n, const double* A, int lda, double* w, double* V, int ldv,
                    int max_sweeps, double tol, hipStream_t s, const int* skip) {
-  k_jacobi<<<1, JT, 0, s>>>(n, A, lda, w, V, ldv, max_sweeps, tol, skip);
+  const int h = (n + 1) / 2, nt = 64 * (1 + jacobi_aw(h) + jacobi_vw(h));
+  k_jacobi<<<1, nt, 0, s>>>(n, A, lda, w, V, ldv, max_sweeps, tol, skip);
 }
 
 void launch_chol_orth(int n, const double* S, double thr, double* T, double* w, int* ok,
