@@ -375,8 +375,8 @@ int fock_local_apply(ace_ctx* ctx, const void* v_local, const void* psi, int nv,
 /* rho = 2 sum_{i<k} phi_i^2 (Eq. (1)'s closed-shell density). */
 int scf_density(ace_ctx* ctx, const void* phi, int k, void* rho);
 
-/* Hartree potential v_H = dV G (*) rho (one isolated Poisson solve, Sec. 3.1).  Allocates a
- * scratch volume and synchronises the stream. */
+/* Hartree potential v_H = dV G (*) rho (one isolated Poisson solve, Sec. 3.1).  Takes a scratch
+ * volume from the context's workspace and synchronises the stream. */
 int hartree_potential(ace_ctx* ctx, const void* rho, void* v_h);
 
 /* Kinetic preconditioner z ~ (T + shift)^{-1} r for nv vectors: z_0 = r / (d + shift) with

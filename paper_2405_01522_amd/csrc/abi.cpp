@@ -190,7 +190,7 @@ int ace_ctx_destroy(ace_ctx* c) {
   c->trace.stream = c->stream;
   c->trace.release();
   for (Buf* b : {&c->work, &c->vbuf, &c->wbuf, &c->part, &c->small, &c->pairs, &c->tda,
-                 &c->part2, &c->ybuf})
+                 &c->part2, &c->ybuf, &c->scf})
     if (b->p) (void)hipFree(b->p);
   if (c->ghat64) (void)hipFree(c->ghat64);
   if (c->ghat32) (void)hipFree(c->ghat32);
@@ -198,6 +198,7 @@ int ace_ctx_destroy(ace_ctx* c) {
   if (c->gpos) (void)hipFree(c->gpos);
   if (c->status) (void)hipFree(c->status);
   if (c->pinned_pairs) (void)hipHostFree(c->pinned_pairs);
+  if (c->pinned_scf) (void)hipHostFree(c->pinned_scf);
   free_blob(c->tda_items);
   delete c;
   return ACE_OK;

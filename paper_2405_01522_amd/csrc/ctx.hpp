@@ -169,6 +169,10 @@ struct ace_ctx {
   // ace_build_apply: Gram partials of W^H psi (M's are in `part` at the same time) and the
   // reduced W^H psi dV
   ace::host::Buf part2, ybuf;
+  // Workspace of the SCF pieces (block eigensolver, Hartree and preconditioner scratch): as large
+  // as the largest call so far, used by one call at a time, freed with the context.
+  ace::host::Buf scf;
+  double* pinned_scf = nullptr;             // landing place of the eigensolver's host values
   ace::host::Blob tda_items;                // pair pointers of the TDA solves
   std::vector<int> pairs_cached;
   int* pinned_pairs = nullptr;
