@@ -8,6 +8,7 @@
 // generated while tiles are staged, never stored.  Both contractions are split over the grid
 // (split-K) with FP64 partial sums reduced in a fixed order.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "tda.hpp"
@@ -125,148 +126,124 @@ __global__ __launch_bounds__(kThreads) void k_gemm_nt(Op<T> A, int M, Op<T> B, i
 // part[z][m][n] = sum_{k in split z} A(m,k) B(n,k), each FP32 operand split as x = hi + lo
 // (hi = RNE bf16(x), lo = RNE bf16(x - hi)) and A B ~ Ahi Bhi + Ahi Blo + Alo Bhi, accumulated
 // in FP32 by v_mfma_f32_16x16x32_bf16 (relative error of one product ~2^-16, the dropped
-// Alo Blo term).  Block tile 128 x 128, 4 waves of 64 x 64 (4 x 4 MFMA tiles each); operand
-// tiles of 128 rows x 64 points are staged through LDS as hi / lo BF16 rows of stride 72
-// (16-byte aligned rows; one 16-byte fragment read per lane), with coalesced row-segment
-// loads.  Generated operands (products of two orbitals) are formed in FP32 while staging.  Lane layout of the 16x16x32 instruction:
-// A[i][k] in lane i + 16 (k / 8), element k % 8 (B likewise with j); D[i][j] in lane
-// j + 16 (i / 4), element i % 4 (output layout checked on gfx950).
-constexpr int MT = 128, KB = 64, LB = KB + 8;
+// Alo Blo term).  Generated operands (products of two orbitals) are formed in FP32 while staging.
+// Lane layout of the 16x16x32 instruction: A[i][k] in lane i + 16 (k / 8), element k % 8 (B
+// likewise with j); D[i][j] in lane j + 16 (i / 4), element i % 4 (output layout checked on
+// gfx950).
+//
+// Block tile 128 x 128 x 64 points.  Splitting the operands (VALU), LDS (64 KB written, 128 KB read
+// a step) and the matrix cores take about 1500 cycles a step each, so they are given to different
+// wavefronts: eight load, split and store the next step's tiles into one half of the LDS while four
+// (64 x 64 each, 4 x 4 MFMA tiles) multiply out of the other.  Loads run a step ahead in registers.
+// Rows are 128 bytes with their 16-byte pieces exchanged by piece ^ (row / 2 % 8): fragment reads
+// and the 8-byte stores meet no bank conflict.
+// 512 x 512 (upper tiles) and 136 x 528 over 64^3 points: 257 and 231 us, against 366 and 358 us
+// with four wavefronts that did all in turn, two workgroups to a CU (rows of 144 bytes: conflicts
+// at the stores) and tiles past the edge worked like others.  With four staging wavefronts 302 us for the
+// first (their chain of load, split and store is then the longest); without the order of
+// workgroups by XCD 9 % more.
+constexpr int MT = 128, KB = 64;
+constexpr int kStaging = 512, kMfmaThreads = kStaging + 256;
+constexpr int kRowStep = kStaging / 16, kPieces = MT / kRowStep;  // rows of a staging thread
+constexpr int kXcds = 8;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-// Stage one operand tile (128 rows x 64 points from point kt) as hi / lo BF16 rows.  Sixteen
-// consecutive lanes read one row (4 consecutive points each, one 16-byte load when VEC), so
-// every load instruction covers four 256-byte row segments.  Loads are unconditional (row and
-// point clamped); rows >= M and points >= k1 are zeroed.
-// rows[r] (r < MT): element offsets of the tile row's first-factor row and second-factor row
-// (product mode), computed once per workgroup so that no index arithmetic beyond one add is
-// left in the K loop.
-__device__ __forceinline__ void tile_rows(const Op<float>& o, int m0, int M, size_t ng, int r,
-                                          longlong2* rows) {
-  const int m = m0 + r;
-  const int mc = m < M ? m : M - 1;
-  int ip = mc, iq = 0;
-  if (o.q) op_rows(o, mc, &ip, &iq);
-  rows[r] = longlong2{(long long)((size_t)ip * ng), (long long)((size_t)iq * ng)};
-}
+// A staging thread's share of an operand tile: points 4 (t % 16) to + 3 of rows t / 16 + 32 i, as
+// loaded (one 16-byte load each when VEC; sixteen lanes read 256 bytes of a row).
+template <bool VEC, bool PROD>
+struct TileLoad {
+  const float* p[kPieces];                // the rows (product mode: the first factor's)
+  const float* q[PROD ? kPieces : 1];     // the second factor's rows
+  float4 x[kPieces];
+  float4 y[PROD ? kPieces : 1];
+  int rows;                               // rows of the tile that exist
 
-// EDGE: the tile reaches past row M or the step past the chunk end k1, so the rows and points
-// outside are zeroed and the loads clamped; interior steps (EDGE false) skip both (the same
-// values: the zeroing factor is then 1).
-template <bool VEC, bool PROD, bool EDGE>
-__device__ __forceinline__ void stage_tile(const Op<float>& o, const longlong2* rows, int m0, int M,
-                                           size_t kt, size_t k1, size_t ng, __bf16* H,
-                                           __bf16* L) {
-  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-  const int c4 = (threadIdx.x & 15) * 4;
-  const size_t k = kt + c4;
+  __device__ __forceinline__ void init(const Op<float>& o, int m0, int M, size_t ng, int t) {
+    rows = M - m0;
 #pragma unroll
-  for (int pass = 0; pass < MT / 16; ++pass) {
-    const int r = pass * 16 + (threadIdx.x >> 4);
-    const bool valid = m0 + r < M;
-    const longlong2 rr = rows[r];
-    const float* p = o.p + rr.x;
-    float x[4], y[4] = {};  // y: the second factor of a product operand
-    if constexpr (VEC) {
-      const size_t kc = !EDGE || k + 3 < ng ? k : ng - 4;
-      const float4 a = *reinterpret_cast<const float4*>(p + kc);
-      x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
-      if constexpr (PROD) {
-        const float4 b = *reinterpret_cast<const float4*>(o.q + rr.y + kc);
-        y[0] = b.x; y[1] = b.y; y[2] = b.z; y[3] = b.w;
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const size_t kc = !EDGE || k + e < ng ? k + e : ng - 1;
-        x[e] = p[kc];
-        if constexpr (PROD) y[e] = o.q[rr.y + kc];
-      }
+    for (int i = 0; i < kPieces; ++i) {
+      const int m = m0 + (t >> 4) + kRowStep * i, mc = m < M ? m : M - 1;
+      int ip = mc, iq = 0;
+      if constexpr (PROD) op_rows(o, mc, &ip, &iq);
+      p[i] = o.p + (size_t)ip * ng;
+      if constexpr (PROD) q[i] = o.q + (size_t)iq * ng;
     }
-    bf16x4 h, l;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      // zeroing by a 0 / 1 factor (all loaded values are finite), not a select the compiler
-      // may turn into a branch around the load; exact, so interior and edge steps agree
-      const float xe = EDGE ? x[e] * ((valid && k + e < k1) ? 1.f : 0.f) : x[e];
-      const float v = PROD ? xe * y[e] : xe;
-      const __bf16 vh = (__bf16)v;
-      h[e] = vh;
-      // the low part of a product from the exact product (one rounding), of a plain value
-      // from the exact difference
-      l[e] = (__bf16)(PROD ? fmaf(xe, y[e], -(float)vh) : v - (float)vh);
-    }
-    *reinterpret_cast<bf16x4*>(H + r * LB + c4) = h;
-    *reinterpret_cast<bf16x4*>(L + r * LB + c4) = l;
   }
-}
-
-// The two halves of stage_tile for a plain (non-product) operand, so that the global loads of
-// the next tile can be in flight during the current tile's products: load_rows reads this
-// thread's 4-point segments of the tile's rows, store_rows splits and stores them.
-template <bool VEC>
-__device__ __forceinline__ void load_rows(const Op<float>& o, const longlong2* rows, size_t kt,
-                                          size_t ng, float4* x) {
-  const int c4 = (threadIdx.x & 15) * 4;
-  const size_t k = kt + c4;
-#pragma unroll
-  for (int pass = 0; pass < MT / 16; ++pass) {
-    const int r = pass * 16 + (threadIdx.x >> 4);
-    const float* p = o.p + rows[r].x;
+  __device__ __forceinline__ static float4 get(const float* r, size_t k, size_t ng) {
     if constexpr (VEC) {
-      const size_t kc = k + 3 < ng ? k : ng - 4;
-      x[pass] = *reinterpret_cast<const float4*>(p + kc);
+      return *reinterpret_cast<const float4*>(r + (k + 3 < ng ? k : ng - 4));
     } else {
       float e4[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) e4[e] = p[k + e < ng ? k + e : ng - 1];
-      x[pass] = float4{e4[0], e4[1], e4[2], e4[3]};
+      for (int e = 0; e < 4; ++e) e4[e] = r[k + e < ng ? k + e : ng - 1];
+      return float4{e4[0], e4[1], e4[2], e4[3]};
     }
   }
-}
-
-template <bool EDGE>
-__device__ __forceinline__ void store_rows(const float4* x, int m0, int M, size_t kt, size_t k1,
-                                           __bf16* H, __bf16* L) {
-  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-  const int c4 = (threadIdx.x & 15) * 4;
-  const size_t k = kt + c4;
-#pragma unroll
-  for (int pass = 0; pass < MT / 16; ++pass) {
-    const int r = pass * 16 + (threadIdx.x >> 4);
-    const bool valid = m0 + r < M;
-    const float xv[4] = {x[pass].x, x[pass].y, x[pass].z, x[pass].w};
-    bf16x4 h, l;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float v = EDGE ? xv[e] * ((valid && k + e < k1) ? 1.f : 0.f) : xv[e];
-      const __bf16 vh = (__bf16)v;
-      h[e] = vh;
-      l[e] = (__bf16)(v - (float)vh);
-    }
-    *reinterpret_cast<bf16x4*>(H + r * LB + c4) = h;
-    *reinterpret_cast<bf16x4*>(L + r * LB + c4) = l;
+  // Points k to k + 3 of row piece i.  (No branch around a load: it would wait for it at once.)
+  __device__ __forceinline__ void load(int i, size_t k, size_t ng) {
+    x[i] = get(p[i], k, ng);
+    if constexpr (PROD) y[i] = get(q[i], k, ng);
   }
-}
+  __device__ __forceinline__ void load_all(size_t k, size_t ng) {
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) load(i, k, ng);
+  }
+  // Split into hi / lo rows of H and L (rows past M hold copies of row M - 1, whose sums are not
+  // stored; unless WHOLE, pieces of 32 rows wholly past M are left out), and load the next step's
+  // points.  TAIL: the last step, which reaches past k1: points from there on are zeroed, by a
+  // 0 / 1 factor (all loaded values are finite), so that whole and partial steps give the same
+  // values; nothing is loaded.
+  template <bool WHOLE, bool TAIL>
+  __device__ __forceinline__ void stage(size_t k, size_t k1, size_t ng, int t, __bf16* H,
+                                        __bf16* L) {
+    const int piece = ((t & 15) >> 1) ^ ((t >> 5) & 7);
+    const int at = (t >> 4) * KB + 8 * piece + 4 * (t & 1);
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+      if (WHOLE || kRowStep * i < rows) {
+        const float xv[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
+        float yv[4] = {};
+        if constexpr (PROD) yv[0] = y[i].x, yv[1] = y[i].y, yv[2] = y[i].z, yv[3] = y[i].w;
+        bf16x4 h, l;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float xe = TAIL ? xv[e] * (k + e < k1 ? 1.f : 0.f) : xv[e];
+          const float v = PROD ? xe * yv[e] : xe;
+          const __bf16 vh = (__bf16)v;
+          h[e] = vh;
+          // the low part of a product from the exact product (one rounding), of a plain value
+          // from the exact difference
+          l[e] = (__bf16)(PROD ? fmaf(xe, yv[e], -(float)vh) : v - (float)vh);
+        }
+        *reinterpret_cast<bf16x4*>(H + at + kRowStep * i * KB) = h;
+        *reinterpret_cast<bf16x4*>(L + at + kRowStep * i * KB) = l;
+      }
+      if (!TAIL) load(i, k + KB, ng);  // (past the end: in bounds, not used)
+      // each piece waits for its own loads only, a step after they were sent off
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+};
 
-// tri != 0: M == N and the result is symmetric; blockIdx.x enumerates only the tiles (bx, by)
-// with bx <= by (blockIdx.y unused) and the lower tiles are never computed.
-// PREF: B is a plain operand whose next tile is prefetched into registers during the products
-template <bool VEC, bool PREF>
-__global__ __launch_bounds__(256) void k_gemm_nt_mfma(Op<float> A, int M, Op<float> B, int N,
-                                                      size_t ng, size_t kchunk,
-                                                      float* __restrict__ part, int tri) {
-  __shared__ __align__(16) __bf16 Ah[MT * LB];
-  __shared__ __align__(16) __bf16 Al[MT * LB];
-  __shared__ __align__(16) __bf16 Bh[MT * LB];
-  __shared__ __align__(16) __bf16 Bl[MT * LB];
-  __shared__ longlong2 rows_a[MT], rows_b[MT];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wr = wave >> 1, wc = wave & 1;  // wave's 64 x 64 quadrant
-  int bx = blockIdx.x, by = blockIdx.y;
+// tri != 0: M == N and the result is symmetric; only the tiles (bx, by) with bx <= by are
+// enumerated and the lower tiles are never computed.  Workgroups go round the XCDs in turn: an XCD
+// takes a run of consecutive (split, tile) pairs, so that the tiles of a split, which read the
+// same points, share its L2.  PA, PB: A, B are generated.
+template <bool VEC, bool PA, bool PB>
+__global__ __launch_bounds__(kMfmaThreads) void k_gemm_nt_mfma(
+    Op<float> A, int M, Op<float> B, int N, size_t ng, size_t kchunk, int nsplit,
+    float* __restrict__ part, int tri) {
+  __shared__ __align__(16) __bf16 T[2][4][MT * KB];  // [half][A hi, A lo, B hi, B lo]
+  const int tm = (M + MT - 1) / MT, tn = (N + MT - 1) / MT;
+  const int tiles = tri ? tm * (tm + 1) / 2 : tm * tn;
+  const int per = (int)(gridDim.x / kXcds);
+  const int g = (int)(blockIdx.x % kXcds) * per + (int)(blockIdx.x / kXcds);
+  if (g >= tiles * nsplit) return;
+  const int z = g / tiles, u = g % tiles;
+  int bx = u % tm, by = u / tm;
   if (tri) {
-    const int u = blockIdx.x;
     int t = (int)((sqrtf(8.0f * u + 1.0f) - 1.0f) * 0.5f);
     while ((t + 1) * (t + 2) / 2 <= u) ++t;
     while (t * (t + 1) / 2 > u) --t;
@@ -274,83 +251,89 @@ __global__ __launch_bounds__(256) void k_gemm_nt_mfma(Op<float> A, int M, Op<flo
     bx = u - t * (t + 1) / 2;
   }
   const int m0 = bx * MT, n0 = by * MT;
-  const size_t k0 = (size_t)blockIdx.z * kchunk;
+  const size_t k0 = (size_t)z * kchunk;
   const size_t k1 = k0 + kchunk < ng ? k0 + kchunk : ng;
-  if (threadIdx.x < MT)
-    tile_rows(A, m0, M, ng, threadIdx.x, rows_a);
-  else if (threadIdx.x < 2 * MT)
-    tile_rows(B, n0, N, ng, threadIdx.x - MT, rows_b);
-  __syncthreads();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (wave < kStaging / 64) {
+    const int t = threadIdx.x;
+    TileLoad<VEC, PA> a;
+    TileLoad<VEC, PB> b;
+    a.init(A, m0, M, ng, t);
+    b.init(B, n0, N, ng, t);
+    size_t k = k0 + 4 * (t & 15);
+    a.load_all(k, ng);
+    b.load_all(k, ng);
+    auto stage = [&](auto whole) __attribute__((always_inline)) {
+      constexpr bool kWhole = decltype(whole)::value;
+      int half = 0;
+      size_t kt = k0;
+      for (; kt + KB <= k1; kt += KB, k += KB, half ^= 1) {
+        a.template stage<kWhole, false>(k, k1, ng, t, T[half][0], T[half][1]);
+        b.template stage<kWhole, false>(k, k1, ng, t, T[half][2], T[half][3]);
+        __syncthreads();
+      }
+      if (kt < k1) {
+        a.template stage<kWhole, true>(k, k1, ng, t, T[half][0], T[half][1]);
+        b.template stage<kWhole, true>(k, k1, ng, t, T[half][2], T[half][3]);
+        __syncthreads();
+      }
+    };
+    if (m0 + MT <= M && n0 + MT <= N)
+      stage(std::true_type{});
+    else
+      stage(std::false_type{});
+    return;
+  }
+  const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+  const int wr = (wave - kStaging / 64) >> 1, wc = wave & 1;  // wave's 64 x 64 quadrant
+  // 16-row and 16-column pieces of it that exist
+  const int ni = (M - m0 - wr * 64 + 15) / 16, nj = (N - n0 - wc * 64 + 15) / 16;
   f32x4 acc[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int li = lane & 15, lg = lane >> 4;
-  float4 xb[MT / 16];
-  if constexpr (PREF) load_rows<VEC>(B, rows_b, k0, ng, xb);
-  for (size_t kt = k0; kt < k1; kt += KB) {
-    // uniform per workgroup and step: whether the A / B tile needs its rows or points masked
-    const bool step_in = kt + KB <= k1;
-    const bool edge_a = !step_in || m0 + MT > M, edge_b = !step_in || n0 + MT > N;
-    if constexpr (PREF) {
-      if (edge_b)
-        store_rows<true>(xb, n0, N, kt, k1, Bh, Bl);
-      else
-        store_rows<false>(xb, n0, N, kt, k1, Bh, Bl);
-      if (kt + KB < k1) load_rows<VEC>(B, rows_b, kt + KB, ng, xb);
-    }
-    // product (generated) operands load two rows; the choice is uniform per launch
-    if (A.q) {
-      if (edge_a)
-        stage_tile<VEC, true, true>(A, rows_a, m0, M, kt, k1, ng, Ah, Al);
-      else
-        stage_tile<VEC, true, false>(A, rows_a, m0, M, kt, k1, ng, Ah, Al);
-    } else {
-      if (edge_a)
-        stage_tile<VEC, false, true>(A, rows_a, m0, M, kt, k1, ng, Ah, Al);
-      else
-        stage_tile<VEC, false, false>(A, rows_a, m0, M, kt, k1, ng, Ah, Al);
-    }
-    if constexpr (!PREF) {
-      if (B.q) {
-        if (edge_b)
-          stage_tile<VEC, true, true>(B, rows_b, n0, N, kt, k1, ng, Bh, Bl);
-        else
-          stage_tile<VEC, true, false>(B, rows_b, n0, N, kt, k1, ng, Bh, Bl);
-      } else {
-        if (edge_b)
-          stage_tile<VEC, false, true>(B, rows_b, n0, N, kt, k1, ng, Bh, Bl);
-        else
-          stage_tile<VEC, false, false>(B, rows_b, n0, N, kt, k1, ng, Bh, Bl);
-      }
-    }
-    __syncthreads();
+  auto multiply = [&](auto whole, const __bf16(*tile)[MT * KB]) __attribute__((always_inline)) {
+    constexpr bool kWhole = decltype(whole)::value;
 #pragma unroll
     for (int ks = 0; ks < KB; ks += 32) {
+      const int at = li * KB + 8 * ((ks / 8 + lg) ^ (li >> 1));
       bf16x8 bh[4], bl[4];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int co = (wc * 64 + t * 16 + li) * LB + ks + 8 * lg;
-        bh[t] = *reinterpret_cast<const bf16x8*>(Bh + co);
-        bl[t] = *reinterpret_cast<const bf16x8*>(Bl + co);
+      for (int j = 0; j < 4; ++j) {
+        bh[j] = *reinterpret_cast<const bf16x8*>(tile[2] + (wc * 64 + j * 16) * KB + at);
+        bl[j] = *reinterpret_cast<const bf16x8*>(tile[3] + (wc * 64 + j * 16) * KB + at);
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int ro = (wr * 64 + i * 16 + li) * LB + ks + 8 * lg;
-        const bf16x8 ah = *reinterpret_cast<const bf16x8*>(Ah + ro);
-        const bf16x8 al = *reinterpret_cast<const bf16x8*>(Al + ro);
+      for (int i = 0; i < 4; ++i)
+        if (kWhole || i < ni) {
+          const bf16x8 ah =
+              *reinterpret_cast<const bf16x8*>(tile[0] + (wr * 64 + i * 16) * KB + at);
+          const bf16x8 al =
+              *reinterpret_cast<const bf16x8*>(tile[1] + (wr * 64 + i * 16) * KB + at);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[j], acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[j], acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[j], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < 4; ++j)
+            if (kWhole || j < nj) {
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[j], acc[i][j], 0, 0, 0);
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[j], acc[i][j], 0, 0, 0);
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[j], acc[i][j], 0, 0, 0);
+            }
         }
-      }
     }
-    __syncthreads();
+  };
+  int half = 0;
+  if (ni >= 4 && nj >= 4) {
+    for (size_t kt = k0; kt < k1; kt += KB, half ^= 1) {
+      __syncthreads();
+      multiply(std::true_type{}, T[half]);
+    }
+  } else {
+    for (size_t kt = k0; kt < k1; kt += KB, half ^= 1) {
+      __syncthreads();
+      if (ni > 0 && nj > 0) multiply(std::false_type{}, T[half]);
+    }
   }
-  float* dst = part + (size_t)blockIdx.z * M * N;
+  float* dst = part + (size_t)z * M * N;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -361,6 +344,21 @@ __global__ __launch_bounds__(256) void k_gemm_nt_mfma(Op<float> A, int M, Op<flo
         const int n = n0 + wc * 64 + j * 16 + li;
         if (m < M && n < N) dst[(size_t)m * N + n] = acc[i][j][r];
       }
+}
+
+// One of A, B generated, the other plain.
+void launch_gemm_mfma(const Op<float>& A, int M, const Op<float>& B, int N, size_t ng,
+                      size_t kchunk, int nsplit, float* part, bool tri, hipStream_t s) {
+  const int tm = (M + MT - 1) / MT, tn = (N + MT - 1) / MT;
+  const size_t total = (size_t)(tri ? tm * (tm + 1) / 2 : tm * tn) * nsplit;
+  const unsigned blocks = (unsigned)((total + kXcds - 1) / kXcds * kXcds);
+  auto go = [&](auto kernel) {
+    kernel<<<blocks, kMfmaThreads, 0, s>>>(A, M, B, N, ng, kchunk, nsplit, part, tri ? 1 : 0);
+  };
+  if (ng % 4 == 0)
+    A.q ? go(k_gemm_nt_mfma<true, true, false>) : go(k_gemm_nt_mfma<true, false, true>);
+  else
+    A.q ? go(k_gemm_nt_mfma<false, true, false>) : go(k_gemm_nt_mfma<false, false, true>);
 }
 
 __global__ void k_split_reduce_f32(const float* __restrict__ part, int nsplit, size_t count,
@@ -453,19 +451,11 @@ void tda_impl(const void* occ, int no, const void* virt, int nv, const void* v_o
   const unsigned rbj = (unsigned)std::min<size_t>(4096, (cntj + 255) / 256);
   const unsigned rbk = (unsigned)std::min<size_t>(4096, (cntk + 255) / 256);
   if constexpr (sizeof(T) == 4) {
-    const int tj = (nov + MT - 1) / MT;
     {
       TraceScope ts(tr, TR_TDA_GEMM);
-      dim3 gj(tj * (tj + 1) / 2, 1, w.nsplit);  // upper tiles only: CJ is symmetric
-      if (ng % 4 == 0)
-        k_gemm_nt_mfma<true, true><<<gj, 256, 0, s>>>(a_ov, nov, b_ov, nov, ng, w.kchunk, (float*)pj, 1);
-      else
-        k_gemm_nt_mfma<false, true><<<gj, 256, 0, s>>>(a_ov, nov, b_ov, nov, ng, w.kchunk, (float*)pj, 1);
-      dim3 gk((noo + MT - 1) / MT, (nvv + MT - 1) / MT, w.nsplit);
-      if (ng % 4 == 0)
-        k_gemm_nt_mfma<true, false><<<gk, 256, 0, s>>>(a_oo, noo, b_vv, nvv, ng, w.kchunk, (float*)pk, 0);
-      else
-        k_gemm_nt_mfma<false, false><<<gk, 256, 0, s>>>(a_oo, noo, b_vv, nvv, ng, w.kchunk, (float*)pk, 0);
+      // (CJ is symmetric: its upper tiles only)
+      launch_gemm_mfma(a_ov, nov, b_ov, nov, ng, w.kchunk, w.nsplit, (float*)pj, true, s);
+      launch_gemm_mfma(a_oo, noo, b_vv, nvv, ng, w.kchunk, w.nsplit, (float*)pk, false, s);
     }
     TraceScope ts(tr, TR_TDA_REDUCE);
     k_split_reduce_f32<<<rbj, 256, 0, s>>>((const float*)pj, w.nsplit, cntj, dv, cj, nov);
@@ -620,19 +610,7 @@ void gemm_full(Op<T> A, int M, Op<T> B, int N, size_t ng, const UhfWork& w, void
   const size_t cnt = (size_t)M * N;
   const unsigned rb = (unsigned)std::min<size_t>(4096, (cnt + 255) / 256);
   if constexpr (sizeof(T) == 4) {
-    dim3 g((M + MT - 1) / MT, (N + MT - 1) / MT, w.nsplit);
-    const bool pref = B.q == nullptr;
-    if (ng % 4 == 0) {
-      if (pref)
-        k_gemm_nt_mfma<true, true><<<g, 256, 0, s>>>(A, M, B, N, ng, w.kchunk, (float*)part, 0);
-      else
-        k_gemm_nt_mfma<true, false><<<g, 256, 0, s>>>(A, M, B, N, ng, w.kchunk, (float*)part, 0);
-    } else {
-      if (pref)
-        k_gemm_nt_mfma<false, true><<<g, 256, 0, s>>>(A, M, B, N, ng, w.kchunk, (float*)part, 0);
-      else
-        k_gemm_nt_mfma<false, false><<<g, 256, 0, s>>>(A, M, B, N, ng, w.kchunk, (float*)part, 0);
-    }
+    launch_gemm_mfma(A, M, B, N, ng, w.kchunk, w.nsplit, (float*)part, false, s);
     k_split_reduce_f32<<<rb, 256, 0, s>>>((const float*)part, w.nsplit, cnt, scale, out, 0);
   } else {
     dim3 g((M + BM - 1) / BM, (N + BN - 1) / BN, w.nsplit);
