@@ -276,11 +276,14 @@ def run_tda(mol, steps, warmup):
     ctx.close()
     nov, noo, nvv = no * nv, no * (no + 1) // 2, nv * (nv + 1) // 2
     ng = mol.n ** 3
-    t = (nov + 127) // 128
     # entries of the two contractions: the method's (the upper triangle of the symmetric ov
-    # block, and oo pairs x vv pairs a <= b) and the launched 128 x 128 tiles
+    # block, and oo pairs x vv pairs a <= b) and the launched ones (upper 128 x 128 tiles of the
+    # ov block, all of the other; at the edges in whole 16 x 16 pieces)
     method_entries = nov * (nov + 1) // 2 + noo * nvv
-    launched_entries = (t * (t + 1) // 2 + ((noo + 127) // 128) * ((nvv + 127) // 128)) * 128 * 128
+    up = lambda m: (m + 15) // 16 * 16
+    side = [min(128, up(nov) - r) for r in range(0, nov, 128)]
+    launched_entries = (sum(a * b for j, b in enumerate(side) for a in side[:j + 1])
+                        + up(noo) * up(nvv))
     gemm_ms = kt.get("tda_gemm", (float("nan"), 1))[0]
     sec = gemm_ms * 1e-3
     # each FP32 product is three BF16 products on the matrix cores (hi*hi + hi*lo + lo*hi)
