@@ -12,14 +12,15 @@ namespace ace {
 
 namespace {
 
-// C = alpha op(A) op(B) + beta C, row-major; op(X) = X or X^T.  64 x 64 tiles, 256 threads,
+// C = alpha op(A) op(B) + beta C, row i times rows[i] if given; row-major; op(X) = X or X^T.  64 x 64 tiles, 256 threads,
 // 4 x 4 outputs per thread, K staged 16 at a time through LDS.
 constexpr int GT = 64, GK = 16;
 
 __global__ __launch_bounds__(256) void k_dgemm(int ta, int tb, int M, int N, int K, double alpha,
                                                const double* __restrict__ A, int lda,
                                                const double* __restrict__ B, int ldb,
-                                               double beta, double* __restrict__ C, int ldc) {
+                                               double beta, double* __restrict__ C, int ldc,
+                                               const double* __restrict__ rows) {
   __shared__ double As[GK][GT + 1];
   __shared__ double Bs[GK][GT + 1];
   const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
@@ -57,7 +58,8 @@ __global__ __launch_bounds__(256) void k_dgemm(int ta, int tb, int M, int N, int
       const int m = m0 + ty + 16 * i, n = n0 + tx + 16 * j;
       if (m < M && n < N) {
         double* c = C + (size_t)m * ldc + n;
-        *c = alpha * acc[i][j] + (beta == 0.0 ? 0.0 : beta * *c);
+        const double v = alpha * acc[i][j] + (beta == 0.0 ? 0.0 : beta * *c);
+        *c = rows ? v * rows[m] : v;
       }
     }
 }
@@ -531,9 +533,10 @@ void launch_scale_rows(double* Y, const double* sc, int n, int k, hipStream_t s)
 }
 
 void launch_dgemm(int ta, int tb, int M, int N, int K, double alpha, const double* A, int lda,
-                  const double* B, int ldb, double beta, double* C, int ldc, hipStream_t s) {
+                  const double* B, int ldb, double beta, double* C, int ldc, hipStream_t s,
+                  const double* rows) {
   dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT);
-  k_dgemm<<<grid, 256, 0, s>>>(ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc);
+  k_dgemm<<<grid, 256, 0, s>>>(ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, rows);
 }
 
 void launch_jacobi(int n, const double* A, int lda, double* w, double* V, int ldv,

@@ -7,9 +7,11 @@ namespace ace {
 
 constexpr int kJacobiMax = 64;  // largest order of the one-workgroup Jacobi eigensolver
 
-// C = alpha op(A) op(B) + beta C (row-major; ta / tb select the transpose)
+// C = alpha op(A) op(B) + beta C (row-major; ta / tb select the transpose), row i then times
+// rows[i] (null: 1)
 void launch_dgemm(int ta, int tb, int M, int N, int K, double alpha, const double* A, int lda,
-                  const double* B, int ldb, double beta, double* C, int ldc, hipStream_t s);
+                  const double* B, int ldb, double beta, double* C, int ldc, hipStream_t s,
+                  const double* rows = nullptr);
 
 // eigenvalues ascending in w[n], eigenvectors in the columns of V (ld ldv); n <= kJacobiMax
 // (a non-null skip pointing at a nonzero device int makes the launch a no-op)

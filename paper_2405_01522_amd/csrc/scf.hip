@@ -288,6 +288,72 @@ __global__ __launch_bounds__(kT) void k_combine(const T* __restrict__ V, int mb,
     if (j < kout) out[(size_t)j * ng + r] = acc[j];
 }
 
+// The block eigensolver's update in one pass over V and HV (m vectors each): X_j = sum_i C[i][j] V_i
+// and HX likewise, with PKEPT the new directions P_j, HP_j (the same sums from i = k on), and the
+// residuals R_j = HX_j - lam_j X_j; k <= KO = 16 outputs.  Every sum has k_combine's order and bits.
+// Bound by HBM.  A start (m = 16) and three steps (m = 32, 48, 48) at k = 16 on 64^3: FP32 111 us,
+// FP64 270 us; as four sums and the residuals one after another 186 and 354 us; k = 8, FP32: 54
+// against 103 us.
+template <typename T, int KO, bool PKEPT>
+__global__ __launch_bounds__(kT) void k_ritz_update(const T* __restrict__ V,
+                                                    const T* __restrict__ HV, int k, int m,
+                                                    size_t ng, const double* __restrict__ C,
+                                                    const double* __restrict__ lam,
+                                                    T* __restrict__ X, T* __restrict__ HX,
+                                                    T* __restrict__ P, T* __restrict__ HP,
+                                                    T* __restrict__ R) {
+  __shared__ T cs[kCombineMax * KO];
+  for (int t = threadIdx.x; t < m * KO; t += kT) {
+    const int i = t / KO, j = t % KO;
+    cs[t] = j < k ? (T)C[(size_t)i * k + j] : T(0);
+  }
+  __syncthreads();
+  const size_t r = (size_t)blockIdx.x * kT + threadIdx.x;
+  if (r >= ng) return;
+  T x[KO], hx[KO], p[KO], hp[KO];
+#pragma unroll
+  for (int j = 0; j < KO; ++j) x[j] = hx[j] = p[j] = hp[j] = T(0);
+  auto add = [&](int i, T v, T hv, bool with_p) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < KO; ++j) {
+      const T c = cs[i * KO + j];
+      x[j] += c * v;
+      hx[j] += c * hv;
+      if (with_p) {
+        p[j] += c * v;
+        hp[j] += c * hv;
+      }
+    }
+  };
+  auto run = [&](int i, int end, bool with_p) __attribute__((always_inline)) {
+    for (; i + 4 <= end; i += 4) {
+      T v[4], hv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        v[u] = V[(size_t)(i + u) * ng + r];
+        hv[u] = HV[(size_t)(i + u) * ng + r];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) add(i + u, v[u], hv[u], with_p);
+    }
+    for (; i < end; ++i) add(i, V[(size_t)i * ng + r], HV[(size_t)i * ng + r], with_p);
+  };
+  run(0, k, false);
+  run(k, m, PKEPT);
+#pragma unroll
+  for (int j = 0; j < KO; ++j)
+    if (j < k) {
+      const size_t off = (size_t)j * ng + r;
+      X[off] = x[j];
+      HX[off] = hx[j];
+      if (PKEPT) {
+        P[off] = p[j];
+        HP[off] = hp[j];
+      }
+      R[off] = hx[j] - (T)lam[j] * x[j];
+    }
+}
+
 template <typename T>
 __global__ __launch_bounds__(kT) void k_residual_grid(const T* __restrict__ X, const T* __restrict__ HX,
                                                       const double* __restrict__ lam, size_t ng,
@@ -359,9 +425,12 @@ __global__ __launch_bounds__(kT) void k_from_f32(const float* __restrict__ src, 
 }
 
 __global__ void k_inv_rms(const double* __restrict__ G, int ld, int nv, double ng,
-                          double* __restrict__ scale) {
+                          double* __restrict__ scale, double* __restrict__ diag) {
   const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < nv) scale[v] = 1.0 / sqrt(fmax(G[(size_t)v * ld + v] / ng, 1e-300));
+  if (v >= nv) return;
+  const double g = G[(size_t)v * ld + v];
+  scale[v] = 1.0 / sqrt(fmax(g / ng, 1e-300));
+  if (diag) diag[v] = g;
 }
 
 // ---- one-workgroup FP64 steps ----
@@ -430,11 +499,6 @@ __global__ __launch_bounds__(kT) void k_inv_sqrt_eig(const double* __restrict__ 
     for (int k = 0; k < m; ++k) s += U[(size_t)i * m + k] * f[k] * U[(size_t)j * m + k];
     out[e] = s;
   }
-}
-
-__global__ void k_scale_coeff_rows(double* __restrict__ C, int ldc, const double* __restrict__ D,
-                                   int m, int k) {
-  for (int e = threadIdx.x; e < m * k; e += blockDim.x) C[(size_t)(e / k) * ldc + e % k] *= D[e / k];
 }
 
 __global__ void k_zero_rows(double* __restrict__ C, int ldc, int r, int k) {
@@ -549,6 +613,29 @@ void launch_combine(bool fp64, const void* V, int mb, size_t ng, const double* C
     combine_impl<float>(V, mb, ng, C, ldc, kout, out, s);
 }
 
+template <typename T>
+static void ritz_update_impl(const void* V, const void* HV, int k, int m, size_t ng,
+                             const double* C, const double* lam, void* X, void* HX, void* P,
+                             void* HP, void* R, hipStream_t s) {
+  auto go = [&](auto kernel) {
+    kernel<<<grid_blocks(ng), kT, 0, s>>>((const T*)V, (const T*)HV, k, m, ng, C, lam, (T*)X,
+                                          (T*)HX, (T*)P, (T*)HP, (T*)R);
+  };
+  if (k <= 8)
+    P ? go(k_ritz_update<T, 8, true>) : go(k_ritz_update<T, 8, false>);
+  else
+    P ? go(k_ritz_update<T, 16, true>) : go(k_ritz_update<T, 16, false>);
+}
+
+void launch_ritz_update(bool fp64, const void* V, const void* HV, int k, int m, size_t ng,
+                        const double* C, const double* lam, void* X, void* HX, void* P, void* HP,
+                        void* R, hipStream_t s) {
+  if (fp64)
+    ritz_update_impl<double>(V, HV, k, m, ng, C, lam, X, HX, P, HP, R, s);
+  else
+    ritz_update_impl<float>(V, HV, k, m, ng, C, lam, X, HX, P, HP, R, s);
+}
+
 void launch_residual_grid(bool fp64, const void* X, const void* HX, const double* lam, int k,
                           size_t ng, void* R, hipStream_t s) {
   dim3 grid(grid_blocks(ng), k);
@@ -622,8 +709,9 @@ void launch_from_f32(bool fp64, const float* src, size_t count, void* dst, hipSt
     k_from_f32<float><<<nb, kT, 0, s>>>(src, count, (float*)dst);
 }
 
-void launch_inv_rms(const double* G, int ld, int nv, double ng, double* scale, hipStream_t s) {
-  k_inv_rms<<<(nv + 63) / 64, 64, 0, s>>>(G, ld, nv, ng, scale);
+void launch_inv_rms(const double* G, int ld, int nv, double ng, double* scale, hipStream_t s,
+                    double* diag) {
+  k_inv_rms<<<(nv + 63) / 64, 64, 0, s>>>(G, ld, nv, ng, scale, diag);
 }
 
 void launch_sym_scale(const double* S, const double* G, int m, double* Ss, double* Gs,
@@ -643,10 +731,6 @@ void launch_drop_diag(double* A, int m, const double* w, double rel, hipStream_t
 void launch_inv_sqrt_from_eig(const double* w, const double* U, int m, double* out,
                               hipStream_t s) {
   k_inv_sqrt_eig<<<1, kT, 0, s>>>(w, U, m, out);
-}
-
-void launch_scale_coeff_rows(double* C, int ldc, const double* D, int m, int k, hipStream_t s) {
-  k_scale_coeff_rows<<<1, kT, 0, s>>>(C, ldc, D, m, k);
 }
 
 void launch_zero_rows(double* C, int ldc, int r, int k, hipStream_t s) {

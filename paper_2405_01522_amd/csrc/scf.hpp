@@ -38,6 +38,14 @@ void launch_abs_diff_sum(bool fp64, const void* a, const void* b, size_t count, 
 void launch_combine(bool fp64, const void* V, int mb, size_t ng, const double* C, int ldc,
                     int kout, void* out, hipStream_t s);
 
+// X_j = sum_{i < m} C[i * k + j] V_i and HX_j likewise from HV; P_j, HP_j (both or none null) the
+// same sums from i = k on; R_j = HX_j - lam_j X_j.  j < k <= kRitzMax, k <= m <= kCombineMax; the
+// outputs overlap neither V nor HV nor each other.
+constexpr int kRitzMax = 16;
+void launch_ritz_update(bool fp64, const void* V, const void* HV, int k, int m, size_t ng,
+                        const double* C, const double* lam, void* X, void* HX, void* P, void* HP,
+                        void* R, hipStream_t s);
+
 // R_j = HX_j - lam_j X_j
 void launch_residual_grid(bool fp64, const void* X, const void* HX, const double* lam, int k,
                           size_t ng, void* R, hipStream_t s);
@@ -61,8 +69,10 @@ void launch_fill(bool fp64, double value, size_t count, void* dst, hipStream_t s
 // dst_v = src_v (float) converted to the grid precision
 void launch_from_f32(bool fp64, const float* src, size_t count, void* dst, hipStream_t s);
 
-// scale_v = 1 / sqrt(max(G[v * ld + v] / ng, tiny)) (inverse RMS from a Gram diagonal)
-void launch_inv_rms(const double* G, int ld, int nv, double ng, double* scale, hipStream_t s);
+// scale_v = 1 / sqrt(max(G[v * ld + v] / ng, tiny)) (inverse RMS from a Gram diagonal); diag (may
+// be null) receives the diagonal itself
+void launch_inv_rms(const double* G, int ld, int nv, double ng, double* scale, hipStream_t s,
+                    double* diag = nullptr);
 
 // ---- small dense steps (one workgroup each) ----
 // D_i = S_ii^{-1/2} (0 if S_ii <= 0); Ss = D S D, Gs = D sym(G) D   (m x m)
@@ -77,8 +87,6 @@ void launch_drop_diag(double* A, int m, const double* w, double rel, hipStream_t
 // out = U diag(f(w)) U^T, f(w) = w^{-1/2} (w > 0; else 0)
 void launch_inv_sqrt_from_eig(const double* w, const double* U, int m, double* out,
                               hipStream_t s);
-// C[i][j] *= D[i] for i < m, j < k (rows of a coefficient matrix, ld ldc)
-void launch_scale_coeff_rows(double* C, int ldc, const double* D, int m, int k, hipStream_t s);
 // zero rows [0, r) of C (m x k, ld ldc)
 void launch_zero_rows(double* C, int ldc, int r, int k, hipStream_t s);
 // out[j] = A[j * ld + j]

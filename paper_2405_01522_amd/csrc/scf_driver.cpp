@@ -211,8 +211,7 @@ struct Eig {
     launch_dgemm(0, 0, m, m, m, 1.0, TG.d(), m, T.d(), m, 0.0, A.d(), m, s);
     launch_drop_diag(A.d(), m, ws.d(), rel, s);
     launch_jacobi(m, A.d(), m, th.d(), Y.d(), m, 60, jtol, s);
-    launch_dgemm(0, 0, m, k, m, 1.0, T.d(), m, Y.d(), m, 0.0, Cm.d(), k, s);
-    launch_scale_coeff_rows(Cm.d(), k, D.d(), m, k, s);
+    launch_dgemm(0, 0, m, k, m, 1.0, T.d(), m, Y.d(), m, 0.0, Cm.d(), k, s, D.d());
   }
 
   // preconditioned residual blocks from the k residuals in R (scale = their inverse RMS):
@@ -233,11 +232,11 @@ struct Eig {
 
   // residuals of the current Ritz pairs (V[0:k], th) into R; norms to h_rd (host, dV norm) and
   // the Ritz values to h_th
-  int residuals(double* maxres) {
-    launch_residual_grid(fp64, V.p, HV.p, th.d(), k, ng, R.p, s);
+  // (have_r: R holds them already)
+  int residuals(bool have_r, double* maxres) {
+    if (!have_r) launch_residual_grid(fp64, V.p, HV.p, th.d(), k, ng, R.p, s);
     gram(R.p, k, R.p, k, 1.0, Gr.d());
-    launch_inv_rms(Gr.d(), k, k, (double)ng, scale.d(), s);
-    launch_diag(Gr.d(), k, k, rd.d(), s);
+    launch_inv_rms(Gr.d(), k, k, (double)ng, scale.d(), s, rd.d());
     if (hipMemcpyAsync(c->pinned_scf, rd.p, 2 * sizeof(double) * kJacobiMax, hipMemcpyDeviceToHost,
                        s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
@@ -254,6 +253,30 @@ struct Eig {
     return ACE_OK;
   }
 
+  // The k lowest Ritz vectors and F times them from m basis vectors, and with keep_p the new
+  // search directions (the update's part outside the first k vectors), into V and HV.  True if R
+  // holds the residuals as well: one pass up to kRitzMax vectors; with more, a thread's four sums
+  // no longer fit its registers, and they are formed one after another.
+  bool update(int m, bool keep_p) {
+    const int pb = (1 + nw) * k;  // first vector of the P block
+    const bool once = k <= kRitzMax;
+    if (once) {
+      launch_ritz_update(fp64, V.p, HV.p, k, m, ng, Cm.d(), th.d(), V2.p, HV2.p,
+                         keep_p ? vec(V2, pb) : nullptr, keep_p ? vec(HV2, pb) : nullptr, R.p, s);
+    } else {
+      launch_combine(fp64, V.p, m, ng, Cm.d(), k, k, V2.p, s);
+      launch_combine(fp64, HV.p, m, ng, Cm.d(), k, k, HV2.p, s);
+      if (keep_p) {
+        const double* c = Cm.d() + (size_t)k * k;
+        launch_combine(fp64, vec(V, k), m - k, ng, c, k, k, vec(V2, pb), s);
+        launch_combine(fp64, vec(HV, k), m - k, ng, c, k, k, vec(HV2, pb), s);
+      }
+    }
+    std::swap(V.p, V2.p);
+    std::swap(HV.p, HV2.p);
+    return once;
+  }
+
   // LOBPCG for the k lowest states of F from the vectors X (overwritten with the Ritz
   // vectors); Ritz values stay in th[0:k] and h_th, residual norms in h_rd.
   int run(const void* vloc, const void* xi, int nxi, void* X, const ace_eig_opts* o,
@@ -267,14 +290,11 @@ struct Eig {
     gram(V.p, k, V.p, k, dv, S.d());
     gram(V.p, k, HV.p, k, dv, G.d());
     rr(k);
-    launch_combine(fp64, V.p, k, ng, Cm.d(), k, k, V2.p, s);
-    launch_combine(fp64, HV.p, k, ng, Cm.d(), k, k, HV2.p, s);
-    std::swap(V.p, V2.p);
-    std::swap(HV.p, HV2.p);
+    bool have_r = update(k, false);
     bool haveP = false;
     int steps = 0;
     for (;;) {
-      rc = residuals(maxres);
+      rc = residuals(have_r, maxres);
       if (rc) return rc;
       if (rec && rec->in && rec->count < rec->cap && (rec->tick++ % rec->stride) == 0) {
         const int nr = std::min(k, rec->cap - rec->count);
@@ -292,15 +312,8 @@ struct Eig {
       gram(V.p, m, V.p, m, dv, S.d());
       gram(V.p, m, HV.p, m, dv, G.d());
       rr(m);
-      launch_combine(fp64, V.p, m, ng, Cm.d(), k, k, V2.p, s);
-      launch_combine(fp64, HV.p, m, ng, Cm.d(), k, k, HV2.p, s);
-      if (mmax > pb) {  // new search directions: the non-X part of the update
-        launch_combine(fp64, vec(V, k), m - k, ng, Cm.d() + (size_t)k * k, k, k, vec(V2, pb), s);
-        launch_combine(fp64, vec(HV, k), m - k, ng, Cm.d() + (size_t)k * k, k, k, vec(HV2, pb), s);
-        haveP = true;
-      }
-      std::swap(V.p, V2.p);
-      std::swap(HV.p, HV2.p);
+      have_r = update(m, mmax > pb);
+      if (mmax > pb) haveP = true;
       ++steps;
       // F V of the kept blocks is carried along by the same combinations as V.  In FP32
       // storage the two drift apart by rounding, step after step, until the computed
@@ -309,6 +322,7 @@ struct Eig {
         rc = fock(vloc, xi, nxi, V.p, k, HV.p);
         if (!rc && haveP) rc = fock(vloc, xi, nxi, vec(V, pb), k, vec(HV, pb));
         if (rc) return rc;
+        have_r = false;
       }
     }
     rc = hip_check(hipMemcpyAsync(X, V.p, vb * k, hipMemcpyDeviceToDevice, s));
