@@ -11,6 +11,16 @@
 
 namespace ace {
 
+// compute units of the current device
+inline int device_cus() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      cus < 1)
+    cus = 256;
+  return cus;
+}
+
 template <typename T>
 struct alignas(2 * sizeof(T)) C2 {
   T r, i;

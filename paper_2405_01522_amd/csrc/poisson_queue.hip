@@ -231,10 +231,8 @@ __global__ __launch_bounds__(kXyQueueThreads) void k_xy_q(const QJob* __restrict
 template <typename Kern>
 int persistent_grid(Kern kernel, int nt, size_t lds, int nitems) {
   allow_lds(kernel, lds);
-  int dev = 0, cus = 0, per_cu = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    cus = 256;
+  const int cus = device_cus();
+  int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel),
                                                    nt, lds) != hipSuccess ||
       per_cu < 1)

@@ -141,7 +141,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm_nt(Op<T> A, int M, Op<T> B, i
 // with four wavefronts that did all in turn, two workgroups to a CU (rows of 144 bytes: conflicts
 // at the stores) and tiles past the edge worked like others.  With four staging wavefronts 302 us for the
 // first (their chain of load, split and store is then the longest); without the order of
-// workgroups by XCD 9 % more.
+// workgroups by XCD 9 % more.  (A workgroup per item instead, on short chunks: 12.8 us for 36 x 528
+// over 16^3 points, 320 items of one step; 11.0 us as below.)
 constexpr int MT = 128, KB = 64;
 constexpr int kStaging = 512, kMfmaThreads = kStaging + 256;
 constexpr int kRowStep = kStaging / 16, kPieces = MT / kRowStep;  // rows of a staging thread
@@ -228,131 +229,152 @@ struct TileLoad {
   }
 };
 
-// tri != 0: M == N and the result is symmetric; only the tiles (bx, by) with bx <= by are
-// enumerated and the lower tiles are never computed.  Workgroups go round the XCDs in turn: an XCD
-// takes a run of consecutive (split, tile) pairs, so that the tiles of a split, which read the
-// same points, share its L2.  PA, PB: A, B are generated.
+// An item of work: tile (bx, by) of the result over the points of split z.  tri != 0: M == N and the
+// result is symmetric; only the tiles with bx <= by are enumerated and the lower tiles are never
+// computed.
+struct TileItem {
+  int m0, n0, z;
+  size_t k0, k1;
+  __device__ __forceinline__ TileItem(int g, int tm, int tiles, int tri, size_t kchunk, size_t ng) {
+    const int u = g % tiles;
+    int bx = u % tm, by = u / tm;
+    if (tri) {
+      int t = (int)((sqrtf(8.0f * u + 1.0f) - 1.0f) * 0.5f);
+      while ((t + 1) * (t + 2) / 2 <= u) ++t;
+      while (t * (t + 1) / 2 > u) --t;
+      by = t;
+      bx = u - t * (t + 1) / 2;
+    }
+    z = g / tiles;
+    m0 = bx * MT;
+    n0 = by * MT;
+    k0 = (size_t)z * kchunk;
+    k1 = k0 + kchunk < ng ? k0 + kchunk : ng;
+  }
+};
+
+// One workgroup per CU (128 KB of LDS) works its items one after the other: the staging wavefronts
+// go on to the next item while the others multiply the last step of this one and store its sums.
+// Workgroups go round the XCDs in turn: an XCD takes a run of consecutive items, so that the tiles
+// of a split, which read the same points, share its L2; every second round backwards, so that no
+// workgroup meets the full tiles of each.  PA, PB: A, B are generated.
 template <bool VEC, bool PA, bool PB>
 __global__ __launch_bounds__(kMfmaThreads) void k_gemm_nt_mfma(
     Op<float> A, int M, Op<float> B, int N, size_t ng, size_t kchunk, int nsplit,
     float* __restrict__ part, int tri) {
   __shared__ __align__(16) __bf16 T[2][4][MT * KB];  // [half][A hi, A lo, B hi, B lo]
   const int tm = (M + MT - 1) / MT, tn = (N + MT - 1) / MT;
-  const int tiles = tri ? tm * (tm + 1) / 2 : tm * tn;
-  const int per = (int)(gridDim.x / kXcds);
-  const int g = (int)(blockIdx.x % kXcds) * per + (int)(blockIdx.x / kXcds);
-  if (g >= tiles * nsplit) return;
-  const int z = g / tiles, u = g % tiles;
-  int bx = u % tm, by = u / tm;
-  if (tri) {
-    int t = (int)((sqrtf(8.0f * u + 1.0f) - 1.0f) * 0.5f);
-    while ((t + 1) * (t + 2) / 2 <= u) ++t;
-    while (t * (t + 1) / 2 > u) --t;
-    by = t;
-    bx = u - t * (t + 1) / 2;
-  }
-  const int m0 = bx * MT, n0 = by * MT;
-  const size_t k0 = (size_t)z * kchunk;
-  const size_t k1 = k0 + kchunk < ng ? k0 + kchunk : ng;
+  const int tiles = tri ? tm * (tm + 1) / 2 : tm * tn, items = tiles * nsplit;
+  const int per = (int)gridDim.x / kXcds, run = (items + kXcds - 1) / kXcds;
+  const int first = (int)(blockIdx.x % kXcds) * run, count = min(run, items - first);
+  const int at = (int)(blockIdx.x / kXcds);
+  auto item_of = [&](int round) { return round * per + (round & 1 ? per - 1 - at : at); };
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int half = 0;
   if (wave < kStaging / 64) {
     const int t = threadIdx.x;
-    TileLoad<VEC, PA> a;
-    TileLoad<VEC, PB> b;
-    a.init(A, m0, M, ng, t);
-    b.init(B, n0, N, ng, t);
-    size_t k = k0 + 4 * (t & 15);
-    a.load_all(k, ng);
-    b.load_all(k, ng);
-    auto stage = [&](auto whole) __attribute__((always_inline)) {
-      constexpr bool kWhole = decltype(whole)::value;
-      int half = 0;
-      size_t kt = k0;
-      for (; kt + KB < k1; kt += KB, k += KB, half ^= 1) {
-        a.template stage<kWhole, false>(k, k1, ng, t, T[half][0], T[half][1]);
-        b.template stage<kWhole, false>(k, k1, ng, t, T[half][2], T[half][3]);
+    for (int round = 0; round * per < count; ++round) {
+      const int i = item_of(round);
+      if (i >= count) continue;
+      const TileItem w(first + i, tm, tiles, tri, kchunk, ng);
+      TileLoad<VEC, PA> a;
+      TileLoad<VEC, PB> b;
+      a.init(A, w.m0, M, ng, t);
+      b.init(B, w.n0, N, ng, t);
+      size_t k = w.k0 + 4 * (t & 15);
+      a.load_all(k, ng);
+      b.load_all(k, ng);
+      auto stage = [&](auto whole) __attribute__((always_inline)) {
+        constexpr bool kWhole = decltype(whole)::value;
+        for (size_t kt = w.k0; kt + KB < w.k1; kt += KB, k += KB, half ^= 1) {
+          a.template stage<kWhole, false>(k, w.k1, ng, t, T[half][0], T[half][1]);
+          b.template stage<kWhole, false>(k, w.k1, ng, t, T[half][2], T[half][3]);
+          __syncthreads();
+        }
+        a.template stage<kWhole, true>(k, w.k1, ng, t, T[half][0], T[half][1]);
+        b.template stage<kWhole, true>(k, w.k1, ng, t, T[half][2], T[half][3]);
         __syncthreads();
-      }
-      if (kt < k1) {
-        a.template stage<kWhole, true>(k, k1, ng, t, T[half][0], T[half][1]);
-        b.template stage<kWhole, true>(k, k1, ng, t, T[half][2], T[half][3]);
-        __syncthreads();
-      }
-    };
-    if (m0 + MT <= M && n0 + MT <= N)
-      stage(std::true_type{});
-    else
-      stage(std::false_type{});
+        half ^= 1;
+      };
+      if (w.m0 + MT <= M && w.n0 + MT <= N)
+        stage(std::true_type{});
+      else
+        stage(std::false_type{});
+    }
     return;
   }
   const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
   const int wr = (wave - kStaging / 64) >> 1, wc = wave & 1;  // wave's 64 x 64 quadrant
-  // 16-row and 16-column pieces of it that exist
-  const int ni = (M - m0 - wr * 64 + 15) / 16, nj = (N - n0 - wc * 64 + 15) / 16;
-  f32x4 acc[4][4];
+  for (int round = 0; round * per < count; ++round) {
+    if (item_of(round) >= count) continue;
+    const TileItem w(first + item_of(round), tm, tiles, tri, kchunk, ng);
+    // 16-row and 16-column pieces of the quadrant that exist
+    const int ni = (M - w.m0 - wr * 64 + 15) / 16, nj = (N - w.n0 - wc * 64 + 15) / 16;
+    f32x4 acc[4][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto multiply = [&](auto whole, const __bf16(*tile)[MT * KB]) __attribute__((always_inline)) {
-    constexpr bool kWhole = decltype(whole)::value;
+      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](auto whole, const __bf16(*tile)[MT * KB]) __attribute__((always_inline)) {
+      constexpr bool kWhole = decltype(whole)::value;
 #pragma unroll
-    for (int ks = 0; ks < KB; ks += 32) {
-      const int at = li * KB + 8 * ((ks / 8 + lg) ^ (li >> 1));
-      bf16x8 bh[4], bl[4];
+      for (int ks = 0; ks < KB; ks += 32) {
+        const int at = li * KB + 8 * ((ks / 8 + lg) ^ (li >> 1));
+        bf16x8 bh[4], bl[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        bh[j] = *reinterpret_cast<const bf16x8*>(tile[2] + (wc * 64 + j * 16) * KB + at);
-        bl[j] = *reinterpret_cast<const bf16x8*>(tile[3] + (wc * 64 + j * 16) * KB + at);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (kWhole || i < ni) {
-          const bf16x8 ah =
-              *reinterpret_cast<const bf16x8*>(tile[0] + (wr * 64 + i * 16) * KB + at);
-          const bf16x8 al =
-              *reinterpret_cast<const bf16x8*>(tile[1] + (wr * 64 + i * 16) * KB + at);
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (kWhole || j < nj) {
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[j], acc[i][j], 0, 0, 0);
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[j], acc[i][j], 0, 0, 0);
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[j], acc[i][j], 0, 0, 0);
-            }
+        for (int j = 0; j < 4; ++j) {
+          bh[j] = *reinterpret_cast<const bf16x8*>(tile[2] + (wc * 64 + j * 16) * KB + at);
+          bl[j] = *reinterpret_cast<const bf16x8*>(tile[3] + (wc * 64 + j * 16) * KB + at);
         }
-    }
-  };
-  int half = 0;
-  if (ni >= 4 && nj >= 4) {
-    for (size_t kt = k0; kt < k1; kt += KB, half ^= 1) {
-      __syncthreads();
-      multiply(std::true_type{}, T[half]);
-    }
-  } else {
-    for (size_t kt = k0; kt < k1; kt += KB, half ^= 1) {
-      __syncthreads();
-      if (ni > 0 && nj > 0) multiply(std::false_type{}, T[half]);
-    }
-  }
-  float* dst = part + (size_t)z * M * N;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i)
+          if (kWhole || i < ni) {
+            const bf16x8 ah =
+                *reinterpret_cast<const bf16x8*>(tile[0] + (wr * 64 + i * 16) * KB + at);
+            const bf16x8 al =
+                *reinterpret_cast<const bf16x8*>(tile[1] + (wr * 64 + i * 16) * KB + at);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wr * 64 + i * 16 + 4 * lg + r;
-        const int n = n0 + wc * 64 + j * 16 + li;
-        if (m < M && n < N) dst[(size_t)m * N + n] = acc[i][j][r];
+            for (int j = 0; j < 4; ++j)
+              if (kWhole || j < nj) {
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[j], acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[j], acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[j], acc[i][j], 0, 0, 0);
+              }
+          }
       }
+    };
+    if (ni >= 4 && nj >= 4) {
+      for (size_t kt = w.k0; kt < w.k1; kt += KB, half ^= 1) {
+        __syncthreads();
+        multiply(std::true_type{}, T[half]);
+      }
+    } else {
+      for (size_t kt = w.k0; kt < w.k1; kt += KB, half ^= 1) {
+        __syncthreads();
+        if (ni > 0 && nj > 0) multiply(std::false_type{}, T[half]);
+      }
+    }
+    float* dst = part + (size_t)w.z * M * N;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = w.m0 + wr * 64 + i * 16 + 4 * lg + r;
+          const int n = w.n0 + wc * 64 + j * 16 + li;
+          if (m < M && n < N) dst[(size_t)m * N + n] = acc[i][j][r];
+        }
+  }
 }
 
 // One of A, B generated, the other plain.
 void launch_gemm_mfma(const Op<float>& A, int M, const Op<float>& B, int N, size_t ng,
                       size_t kchunk, int nsplit, float* part, bool tri, hipStream_t s) {
   const int tm = (M + MT - 1) / MT, tn = (N + MT - 1) / MT;
-  const size_t total = (size_t)(tri ? tm * (tm + 1) / 2 : tm * tn) * nsplit;
-  const unsigned blocks = (unsigned)((total + kXcds - 1) / kXcds * kXcds);
+  const size_t items = (size_t)(tri ? tm * (tm + 1) / 2 : tm * tn) * nsplit;
+  const unsigned blocks =
+      (unsigned)((std::min<size_t>(items, device_cus()) + kXcds - 1) / kXcds * kXcds);
   auto go = [&](auto kernel) {
     kernel<<<blocks, kMfmaThreads, 0, s>>>(A, M, B, N, ng, kchunk, nsplit, part, tri ? 1 : 0);
   };
@@ -568,16 +590,13 @@ size_t tda_workspace_bytes(int no, int nv, size_t ng, bool fp64, TdaWork* w) {
     kchunk = ((kchunk + kSub - 1) / kSub) * kSub;
     if (kchunk < kSub) kchunk = kSub;
   } else {
-    // matrix-core contractions: one wave of workgroups (two per CU, as their LDS allows) for
-    // the larger launch, so no partly filled second wave; K chunks of whole 64-point tiles
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus < 1)
-      cus = 256;
+    // matrix-core contractions: two chunks per CU, which its one workgroup works in turn, for the
+    // larger launch, so that no round is partly filled; K chunks of whole 64-point tiles.  (One
+    // chunk per CU sums twice as many points in FP32: at 64^3 with 16 + 32 orbitals the block's
+    // error against FP64 grows from 5.4e-7 to 9.0e-7.)
     const size_t tj = (nov + MT - 1) / MT;
     const size_t tiles = std::max(tj * (tj + 1) / 2, ((noo + MT - 1) / MT) * ((nvv + MT - 1) / MT));
-    nsplit = std::max<size_t>(1, (size_t)(2 * cus) / tiles);
+    nsplit = std::max<size_t>(1, (size_t)(2 * device_cus()) / tiles);
     kchunk = (ng + nsplit - 1) / nsplit;
     kchunk = ((kchunk + KB - 1) / KB) * KB;
   }
