@@ -126,6 +126,22 @@ __global__ void k_ghat_positions(const double* __restrict__ oct, T* __restrict__
 }
 
 // ---------------------------------------------------------------------------------------
+// The XY pass over grid = (planes, transforms): by halves, or whole planes with NT threads.
+template <typename T, int N, int NT>
+void launch_xy(dim3 grid, C2<T>* w, const T* g, const TwE<T>* t, hipStream_t s) {
+  if constexpr (by_halves<T, N>()) {
+    if (by_halves<T, N>((int)grid.y)) {
+      allow_lds(k_xy_halves<T, N>, halves_lds<T, N>());
+      k_xy_halves<T, N><<<grid, halves_threads<T, N>(), halves_lds<T, N>(), s>>>(w, g, t);
+      return;
+    }
+  }
+  if constexpr (fits<T, N>()) {
+    allow_lds(k_xy<T, N, 1, NT>, planes_lds<T, N>());
+    k_xy<T, N, 1, NT><<<grid, NT, planes_lds<T, N>(), s>>>(w, g, t);
+  }
+}
+
 template <typename T, int N, typename R>
 void run_poisson(bool rp, R res, void* work, const void* ghat, const void* tw, hipStream_t s,
                  Trace* tr) {
@@ -155,14 +171,7 @@ void run_poisson(bool rp, R res, void* work, const void* ghat, const void* tw, h
   }
   {
     TraceScope ts(tr, TR_XY);
-    if constexpr (by_halves<T, N>()) {
-      allow_lds(k_xy_halves<T, N>, halves_lds<T, N>());
-      k_xy_halves<T, N><<<gxy, halves_threads<T, N>(), halves_lds<T, N>(), s>>>(w, gh, t);
-    } else {
-      constexpr int nt = xy_threads<T, N>();
-      allow_lds(k_xy<T, N, 1, nt>, planes_lds<T, N>());
-      k_xy<T, N, 1, nt><<<gxy, nt, planes_lds<T, N>(), s>>>(w, gh, t);
-    }
+    launch_xy<T, N, xy_threads<T, N>()>(gxy, w, gh, t, s);
   }
   {
     TraceScope ts(tr, TR_ZINV);
@@ -237,22 +246,14 @@ static void dispatch_poisson(int n, bool fp64, bool real_packed, R res, void* wo
 template <typename T, int N>
 static void xy_edge(int nt, void* work, int count, const void* gpos, const void* tw,
                     hipStream_t s) {
-  constexpr int P = 2 * N;
-  const size_t lds = planes_lds<T, N>();
-  dim3 grid(P, count);
+  const dim3 grid(2 * N, count);
   C2<T>* w = reinterpret_cast<C2<T>*>(work);
   const T* g = reinterpret_cast<const T*>(gpos);
   const TwE<T>* t = reinterpret_cast<const TwE<T>*>(tw);
-  if constexpr (by_halves<T, N>()) {
-    allow_lds(k_xy_halves<T, N>, halves_lds<T, N>());
-    k_xy_halves<T, N><<<grid, halves_threads<T, N>(), halves_lds<T, N>(), s>>>(w, g, t);
-  } else if (nt == 512) {
-    allow_lds(k_xy<T, N, 1, 512>, lds);
-    k_xy<T, N, 1, 512><<<grid, 512, lds, s>>>(w, g, t);
-  } else {
-    allow_lds(k_xy<T, N, 1, 1024>, lds);
-    k_xy<T, N, 1, 1024><<<grid, 1024, lds, s>>>(w, g, t);
-  }
+  if (nt == 512)
+    launch_xy<T, N, 512>(grid, w, g, t, s);
+  else
+    launch_xy<T, N, 1024>(grid, w, g, t, s);
 }
 
 int launch_xy_edge(int n, bool fp64, int nt, void* work, int count, const void* gpos,

@@ -521,6 +521,16 @@ template <typename T, int N>
 constexpr bool by_halves() {
   return N >= (sizeof(T) == 4 ? 56 : 40);
 }
+// But launches of at most one plane per CU have a CU's LDS for each plane either way, and the whole
+// plane is worked by twice the threads with half the barriers.  XY pass, halves -> whole plane, us:
+// FP32 edge 64, 1 and 2 transforms 13.5 -> 10.8 and 15.4 -> 13.5, edge 56 14.3 -> 10.1 and 16.0 ->
+// 12.4; FP64 edge 48 14.0 -> 10.8 and 15.7 -> 13.0, edge 40, 3 transforms (240 planes), 13.6 -> 11.5.
+// From the next transform on the halves are as fast or faster (edge 40, 4: 18.2 against 18.9).
+template <typename T, int N>
+bool by_halves(int transforms) {
+  if constexpr (!by_halves<T, N>()) return false;
+  return !fits<T, N>() || (long long)transforms * 2 * N > device_cus();
+}
 template <typename T, int N>
 constexpr int halves_threads() {
   return sizeof(T) == 8 && N == 56 ? 768 : 512;
