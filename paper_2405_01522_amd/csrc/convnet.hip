@@ -326,6 +326,8 @@ __global__ __launch_bounds__(kT, 3) void k_conv88(const float* __restrict__ in,
 // the three outputs x - 1, x, x + 1, carried in registers.  64^3 x 16: 153 us as FMAs with the
 // inputs staged in LDS, 67 us here (134 MB read, 2.0 TB/s; the LDS passes and their barriers
 // bound it).
+// An infinite weight times a part that is zero makes a NaN of an infinite product, so a NaN output
+// is formed again from the definition.
 // LOSS: instead of y, writes g = (y - t) / count and the workgroup's sum of (y - t)^2.
 constexpr int MY = 16, MZ = 16;  // lines of a workgroup; it marches over mx planes
 template <bool LOSS>
@@ -365,6 +367,7 @@ __global__ __launch_bounds__(kT) void k_conv81(const float* __restrict__ in,
   const float bias = b[0];
   float r0 = 0.f, r1 = 0.f;  // sums begun for the outputs x' + 1 and x'
   double loss = 0.0;
+  bool nan = false;
   const int xe = min(n, x0 + mx);
   fetch(x0 - 1);
   for (int xp = x0 - 1; xp <= xe; ++xp) {
@@ -409,12 +412,38 @@ __global__ __launch_bounds__(kT) void k_conv81(const float* __restrict__ in,
     r0 = bias + s[0];
     if (xp - 1 >= x0 && mine) {
       const size_t at = blockIdx.y * ng + ((size_t)(xp - 1) * n + y0 + ly) * n + z0 + lz;
+      const bool ok = done == done;
+      nan |= !ok;
       if (LOSS) {
         const float d = done - t[at];
         y[at] = d * inv_count;
-        loss += (double)d * d;
+        loss += ok ? (double)d * d : 0.0;
       } else {
         y[at] = done;
+      }
+    }
+  }
+  if (nan) {
+#pragma unroll 1
+    for (int x = x0; x < xe; ++x) {
+      const size_t at = blockIdx.y * ng + ((size_t)x * n + y0 + ly) * n + z0 + lz;
+      if (y[at] == y[at]) continue;
+      // the weight of (tap, channel j) is element j of operand tap / 16, lane tap % 16
+      float v = bias;
+#pragma unroll 1
+      for (int j = 0; j < C; ++j)
+#pragma unroll 1
+        for (int q = 0; q < 27; ++q) {
+          const int hx = x + q / 9 - 1, hy = y0 + ly + q / 3 % 3 - 1, hz = z0 + lz + q % 3 - 1;
+          const float a = in_box(hx, hy, hz, n) ? inb[(((size_t)hx * n + hy) * n + hz) * C + j] : 0.f;
+          v = fmaf((float)reinterpret_cast<const __bf16*>(wq + q / 16 * 64 + q % 16)[j], a, v);
+        }
+      if (LOSS) {
+        const float d = v - t[at];
+        y[at] = d * inv_count;
+        loss += (double)d * d;
+      } else {
+        y[at] = v;
       }
     }
   }
