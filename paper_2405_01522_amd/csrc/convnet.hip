@@ -484,6 +484,7 @@ __global__ __launch_bounds__(kT, 2) void k_wgrad88(const float* __restrict__ in,
   __shared__ __align__(16) float ti[HX * IY * HZ * C];
   __shared__ __align__(16) float tg[TX * GY * TZ * C];
   static_assert(HX * IY * HZ * C >= 4 * 9 * 256 + 4 * 64, "the sums of the wavefronts fit in the tile");
+  __shared__ int again;
   const size_t ng = (size_t)n * n * n;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 15, kk = lane >> 4;
@@ -515,48 +516,77 @@ __global__ __launch_bounds__(kT, 2) void k_wgrad88(const float* __restrict__ in,
     reinterpret_cast<f32x4*>(ti)[e / (HZ * 2) * IY * HZ * 2 + e % (HZ * 2)] = z4;
   for (int e = threadIdx.x; e < TX * 2 * TZ * 2; e += kT)
     reinterpret_cast<f32x4*>(tg)[(e / (TZ * 4) * GY + (e / (TZ * 2) & 1) * (GY - 1)) * TZ * 2 + e % (TZ * 2)] = z4;
-  double sum[9][4] = {};
-  double gtot = 0.0;
-  if ((int)blockIdx.x < ntile * nb) fetch(blockIdx.x);
-  for (int bt = blockIdx.x; bt < ntile * nb; bt += gridDim.x) {
-    __syncthreads();  // the previous tile's readers are done
-#pragma unroll
-    for (int u = 0; u < LI; ++u) {
-      const int e = threadIdx.x + u * kT, ln = e / (HZ * 2);  // line of HX x HY
-      if (e < NI)
-        reinterpret_cast<f32x4*>(ti)[(ln / HY * IY + ln % HY + 1) * HZ * 2 + e % (HZ * 2)] = fi[u];
-    }
-#pragma unroll
-    for (int u = 0; u < LG; ++u) {
-      const int e = threadIdx.x + u * kT, ln = e / (TZ * 2);
-      reinterpret_cast<f32x4*>(tg)[(ln / TY * GY + ln % TY + 1) * TZ * 2 + e % (TZ * 2)] = fg[u];
-    }
-    __syncthreads();
-    if (bt + (int)gridDim.x < ntile * nb) fetch(bt + gridDim.x);
-    const float* ga = tg + ((wave * GY + col / 8) * TZ + kk) * C + col % 8;
-    const float* ib = ti + ((wave * IY + 2 * (col / 8)) * HZ + kk) * C + col % 8;
-    f32x4 acc[9] = {};
-    float gsum = 0.f;
-#pragma unroll 1
-    for (int ly = 0; ly <= TY; ++ly, ga += TZ * C, ib += HZ * C) {
-#pragma unroll
-      for (int ks = 0; ks < TZ / 4; ++ks) {
-        const float a = ga[ks * 4 * C];
-        gsum += a;
-#pragma unroll
-        for (int q = 0; q < 9; ++q) {  // (dx, dz)
-          const float v = ib[(q / 3 * IY * HZ + q % 3 + ks * 4) * C];
-          acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, v, acc[q], 0, 0, 0);
-        }
-      }
-    }
+  if (threadIdx.x == 0) again = 0;
+  double sum[9][4], gtot;
+  for (bool careful = false;; careful = true) {
+    gtot = 0.0;
 #pragma unroll
     for (int q = 0; q < 9; ++q)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sum[q][r] += acc[q][r];
-    gtot += gsum;
+      for (int r = 0; r < 4; ++r) sum[q][r] = 0.0;
+    if ((int)blockIdx.x < ntile * nb) fetch(blockIdx.x);
+    for (int bt = blockIdx.x; bt < ntile * nb; bt += gridDim.x) {
+      __syncthreads();  // the previous tile's readers are done
+#pragma unroll
+      for (int u = 0; u < LI; ++u) {
+        const int e = threadIdx.x + u * kT, ln = e / (HZ * 2);  // line of HX x HY
+        if (e < NI)
+          reinterpret_cast<f32x4*>(ti)[(ln / HY * IY + ln % HY + 1) * HZ * 2 + e % (HZ * 2)] = fi[u];
+      }
+#pragma unroll
+      for (int u = 0; u < LG; ++u) {
+        const int e = threadIdx.x + u * kT, ln = e / (TZ * 2);
+        reinterpret_cast<f32x4*>(tg)[(ln / TY * GY + ln % TY + 1) * TZ * 2 + e % (TZ * 2)] = fg[u];
+      }
+      __syncthreads();
+      if (bt + (int)gridDim.x < ntile * nb) fetch(bt + gridDim.x);
+      const float* ga = tg + ((wave * GY + col / 8) * TZ + kk) * C + col % 8;
+      const float* ib = ti + ((wave * IY + 2 * (col / 8)) * HZ + kk) * C + col % 8;
+      f32x4 acc[9] = {};
+      float gsum = 0.f;
+#pragma unroll 1
+      for (int ly = 0; ly <= TY; ++ly, ga += TZ * C, ib += HZ * C) {
+        if (careful && ly == TY && kk >= 2) {  // s = 1 ends before its zero line
+#pragma unroll
+          for (int q = 0; q < 9; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sum[q][r] += acc[q][r];
+        }
+#pragma unroll
+        for (int ks = 0; ks < TZ / 4; ++ks) {
+          const float a = ga[ks * 4 * C];
+          gsum += a;
+#pragma unroll
+          for (int q = 0; q < 9; ++q) {  // (dx, dz)
+            const float v = ib[(q / 3 * IY * HZ + q % 3 + ks * 4) * C];
+            acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, v, acc[q], 0, 0, 0);
+          }
+        }
+        if (careful && ly == 0 && kk < 2) {  // s = 0 begins after its zero line
+#pragma unroll
+          for (int q = 0; q < 9; ++q) acc[q] = z4;
+        }
+      }
+      if (!careful || kk < 2) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) sum[q][r] += acc[q][r];
+      }
+      gtot += gsum;
+    }
+    // A zero line of g makes a NaN of an infinite input: where a sum is not finite, all is done once
+    // more with the sums of rows s (lanes with kk / 2 = s) kept from their zero line.  (Kept from it
+    // always: 4 % slower.)
+    bool odd = false;
+#pragma unroll
+    for (int q = 0; q < 9; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) odd |= !__builtin_isfinite(sum[q][r]);
+    if (odd) again = 1;
+    __syncthreads();
+    if (careful || !again) break;
   }
-  __syncthreads();
   float* red = ti;  // [wave][(dx, dz)][row][col], then [wave][lane]
 #pragma unroll
   for (int q = 0; q < 9; ++q)

@@ -72,3 +72,63 @@ def test_infinite_weight(n, layer, tap, value):
     if (layer, tap) == (2, 13):
         loss, _ = net.gradient(torch.from_numpy(x).cuda(), torch.zeros((2, n, n, n), device="cuda"))
         assert loss == np.inf
+
+
+def _gradient(layers, acts, t):
+    """Gradient of each layer's (w, b), each sum product by product over the output's points, with
+    zeros for inputs outside the box."""
+    g = ((acts[-1][0] - t) / t.size)[None]
+    grads = []
+    for li in (2, 1, 0):
+        w = layers[li][0]
+        if li < 2:
+            g = np.where(acts[li + 1] > 0, g, 0.0)
+        gw = np.empty_like(w)
+        ga = np.zeros_like(acts[li])
+        for q in range(27):
+            s = _shift(acts[li], q)
+            for o in range(w.shape[0]):
+                for i in range(w.shape[1]):
+                    gw[o, i, q] = np.sum(g[o] * s[i])
+            gs = _shift(g, 26 - q)
+            for i in range(w.shape[1]):
+                for o in range(w.shape[0]):
+                    ga[i] += w[o, i, q] * gs[o]
+        grads = [gw.reshape(-1), g.sum(axis=(1, 2, 3))] + grads
+        g = ga
+    return np.concatenate(grads)
+
+
+@pytest.mark.parametrize("where", ["inside", "tile edge"])
+def test_gradient_of_an_infinite_input(where):
+    """An infinite input reaches the activations of three points around it, and tile edges
+    (y = 8) among them."""
+    n = 16
+    c = {"inside": (6, 5, 8), "tile edge": (7, 8, 7)}[where]
+    rng = np.random.default_rng(1)
+    layers = _layers(rng)
+    x = rng.integers(1, 4, size=(1, n, n, n)).astype(np.float32)
+    x[0][c] = np.inf
+    t = rng.normal(size=(1, n, n, n)).astype(np.float32)
+    loss, grad = _net(layers).gradient(torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda())
+    assert loss == np.inf
+    with np.errstate(all="ignore"):
+        acts = _forward(layers, x[0].astype(np.float64))
+        ref = _gradient(layers, acts, t[0].astype(np.float64))
+    assert np.array_equal(_kind(grad), _kind(ref)), np.nonzero(_kind(grad) != _kind(ref))
+
+
+@pytest.mark.parametrize("c", [(5, 7, 8)])
+def test_gradient_of_an_infinite_target(c):
+    n = 16
+    rng = np.random.default_rng(2)
+    layers = _layers(rng)
+    x = rng.integers(1, 4, size=(1, n, n, n)).astype(np.float32)
+    t = rng.normal(size=(1, n, n, n)).astype(np.float32)
+    t[0][c] = np.inf
+    loss, grad = _net(layers).gradient(torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda())
+    assert loss == np.inf
+    with np.errstate(all="ignore"):
+        acts = _forward(layers, x[0].astype(np.float64))
+        ref = _gradient(layers, acts, t[0].astype(np.float64))
+    assert np.array_equal(_kind(grad), _kind(ref)), np.nonzero(_kind(grad) != _kind(ref))
