@@ -614,10 +614,13 @@ __global__ __launch_bounds__(kT, 2) void k_wgrad88(const float* __restrict__ in,
 // products: rows = the 27 taps (two products of 16) and a row of ones, which gives sum_p f[p][c]
 // (the bias gradient of the 1 -> 8 layer, SIGN = 1); columns = channels.  SIGN = -1, s = g,
 // f = the input: the 8 -> 1 layer, whose bias gradient sum_p s[p] is added up beside it.
+// For SIGN = -1 the sums run over f's points, and s is zero where p - d_t leaves the box; the layer's
+// own sum, over s's points, has no such product, but one of s[p] with a zero of f outside the box.
+// Both only matter where a value is infinite: such a wavefront forms its sums again point by point.
 // Tiles and sums as in k_wgrad88.  64^3 x 8: 138 us (8 -> 1) and 99 us (1 -> 8) with a thread per
 // output; 31 and 30 us here (75 MB read).
 template <int SIGN>
-__global__ __launch_bounds__(kT) void k_wgrad18(const float* __restrict__ s,
+__global__ __launch_bounds__(kT, 4) void k_wgrad18(const float* __restrict__ s,
                                                 const float* __restrict__ f,
                                                 const float* __restrict__ zero,
                                                 float* __restrict__ part, int n, int tny, int tnz,
@@ -695,6 +698,38 @@ __global__ __launch_bounds__(kT) void k_wgrad18(const float* __restrict__ s,
         const float bv = col < C ? v : 0.f;
         acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(s0[move[0] ? ks * 4 : 0], bv, acc[0], 0, 0, 0);
         acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(s1[move[1] ? ks * 4 : 0], bv, acc[1], 0, 0, 0);
+      }
+    }
+    if (SIGN < 0) {
+      bool odd = false;
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) odd |= !__builtin_isfinite(acc[m][r]);
+      if (__any(odd)) {
+        int x0, y0, z0;
+        tile_origin(bt % ntile, tny, tnz, TX, TY, TZ, &x0, &y0, &z0);
+#pragma unroll 1
+        for (int i = 0; i < 8; ++i) {  // one at a time, for the registers' sake
+          const int t = i / 4 * 16 + 4 * kk + i % 4;
+          const int dx = t / 9 - 1, dy = t / 3 % 3 - 1, dz = t % 3 - 1;
+          float v = 0.f;
+#pragma unroll 1
+          for (int e = 0; e < TY * TZ && t < 27; ++e) {  // the wavefront's points (x = wave)
+            const int py = e / TZ, pz = e % TZ;
+            const int gx = x0 + wave, gy = y0 + py, gz = z0 + pz;
+            if (!in_box(gx, gy, gz, n)) continue;
+            const float* sp = ts + ((wave + 1) * HY + py + 1) * HZ + pz + 1;
+            if (in_box(gx - dx, gy - dy, gz - dz, n))
+              v = fmaf(sp[-((dx * HY + dy) * HZ + dz)],
+                       tf[((wave * TY + py) * TZ + pz) * C + (col & 7)], v);
+            if (!in_box(gx + dx, gy + dy, gz + dz, n)) v = fmaf(sp[0], 0.f, v);
+          }
+#pragma unroll
+          for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[m][r] = i == m * 4 + r ? v : acc[m][r];
+        }
       }
     }
 #pragma unroll

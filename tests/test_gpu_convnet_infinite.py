@@ -99,12 +99,12 @@ def _gradient(layers, acts, t):
     return np.concatenate(grads)
 
 
-@pytest.mark.parametrize("where", ["inside", "tile edge"])
+@pytest.mark.parametrize("where", ["inside", "tile edge", "face", "corner"])
 def test_gradient_of_an_infinite_input(where):
-    """An infinite input reaches the activations of three points around it, and tile edges
-    (y = 8) among them."""
+    """An infinite input reaches the activations of three points around it, across tile edges (y = 8)
+    and on faces of the box."""
     n = 16
-    c = {"inside": (6, 5, 8), "tile edge": (7, 8, 7)}[where]
+    c = {"inside": (6, 5, 8), "tile edge": (7, 8, 7), "face": (0, 7, 8), "corner": (15, 0, 15)}[where]
     rng = np.random.default_rng(1)
     layers = _layers(rng)
     x = rng.integers(1, 4, size=(1, n, n, n)).astype(np.float32)
@@ -118,7 +118,7 @@ def test_gradient_of_an_infinite_input(where):
     assert np.array_equal(_kind(grad), _kind(ref)), np.nonzero(_kind(grad) != _kind(ref))
 
 
-@pytest.mark.parametrize("c", [(5, 7, 8)])
+@pytest.mark.parametrize("c", [(5, 7, 8), (0, 7, 8), (15, 15, 0)])
 def test_gradient_of_an_infinite_target(c):
     n = 16
     rng = np.random.default_rng(2)
