@@ -366,6 +366,14 @@ const char* ace_trace_name(int id);
  *   K       = the exchange operator of Eq. (2) over the occupied spatial orbitals, applied
  *             through ACE (Eqs. (11)-(13)) rebuilt every SCF iteration (Sec. 3.1);
  *   E       = 2 sum_i <phi_i|T + V_ext|phi_i> + 1/2 int rho v_H + sum_i <phi_i|K phi_i>.
+ *
+ * Scratch.  hartree_potential (one volume), kinetic_precondition (nv volumes with sweeps > 1) and
+ * the calls around the block eigensolver -- fock_lowest_states, unocc_states, scf_energies and
+ * scf_run: for k vectors up to 14 k volumes, with ACE_PRECOND_NET 18 k and 2 k of FP32 -- take
+ * theirs from one buffer of the context, as large as the largest call so far.  Up to 1 GiB of it is
+ * kept between calls; it is given up when another allocation of the same context fails, and freed
+ * by ace_ctx_destroy.  (A program short of device memory destroys contexts that it no longer
+ * needs: what a context keeps, other libraries and other contexts cannot use.)
  * ------------------------------------------------------------------------------------- */
 
 /* out_v = (accumulate ? out_v : 0) + T psi_v + v_local psi_v, v < nv (v_local may be NULL). */
@@ -375,8 +383,8 @@ int fock_local_apply(ace_ctx* ctx, const void* v_local, const void* psi, int nv,
 /* rho = 2 sum_{i<k} phi_i^2 (Eq. (1)'s closed-shell density). */
 int scf_density(ace_ctx* ctx, const void* phi, int k, void* rho);
 
-/* Hartree potential v_H = dV G (*) rho (one isolated Poisson solve, Sec. 3.1).  Takes a scratch
- * volume from the context's workspace and synchronises the stream. */
+/* Hartree potential v_H = dV G (*) rho (one isolated Poisson solve, Sec. 3.1).  Synchronises the
+ * stream. */
 int hartree_potential(ace_ctx* ctx, const void* rho, void* v_h);
 
 /* Kinetic preconditioner z ~ (T + shift)^{-1} r for nv vectors: z_0 = r / (d + shift) with

@@ -660,7 +660,7 @@ int davidson_core(ace_ctx* c, const double* Ain, const std::vector<double>& d, i
                   std::make_pair(&nrm, (size_t)k), std::make_pair(&Sm, (size_t)k * k),
                   std::make_pair(&lam, (size_t)k), std::make_pair(&U, (size_t)k * k),
                   std::make_pair(&Y, (size_t)k * n), std::make_pair(&sc, (size_t)k)})
-    if (!rc) rc = pr.first->alloc(pr.second);
+    if (!rc) rc = pr.first->alloc(c, pr.second);
   if (rc) return rc;
   if (hipMemcpyAsync(dd.p, d.data(), sizeof(double) * n, hipMemcpyHostToDevice, s) != hipSuccess ||
       hipMemcpyAsync(V.p, v0.data(), sizeof(double) * v0.size(), hipMemcpyHostToDevice, s) != hipSuccess)
@@ -755,8 +755,8 @@ int tda_excitations_diag(ace_ctx* c, const double* C, const double* d, int n, in
   if (nstates < 1 || nstates > 16 || nstates > n || !(tol > 0.0) || max_iter < 1)
     return ACE_ERR_INVALID;
   DevBuf A, dd;
-  int rc = A.alloc((size_t)n * n);
-  if (!rc) rc = dd.alloc((size_t)n);
+  int rc = A.alloc(c, (size_t)n * n);
+  if (!rc) rc = dd.alloc(c, (size_t)n);
   if (rc) return rc;
   if (hipMemcpyAsync(dd.p, d, sizeof(double) * n, hipMemcpyHostToDevice, c->stream) != hipSuccess)
     return ACE_ERR_HIP;
@@ -778,7 +778,7 @@ int tdhf_excitations(ace_ctx* c, const double* C, const double* B, const double*
                   std::make_pair(&T1, (size_t)n * n), std::make_pair(&H, (size_t)n * n),
                   std::make_pair(&dd, (size_t)n), std::make_pair(&Z, (size_t)nstates * n),
                   std::make_pair(&sc, (size_t)nstates)})
-    if (!rc) rc = pr.first->alloc(pr.second);
+    if (!rc) rc = pr.first->alloc(c, pr.second);
   if (rc) return rc;
   int* info = c->status + 2;  // scratch word of the status area
   if (hipMemsetAsync(info, 0, sizeof(int), s) != hipSuccess ||
@@ -793,7 +793,7 @@ int tdhf_excitations(ace_ctx* c, const double* C, const double* B, const double*
   std::vector<double> dh(n);
   int hinfo = 0;
   DevBuf hd;
-  rc = hd.alloc((size_t)n);
+  rc = hd.alloc(c, (size_t)n);
   if (rc) return rc;
   launch_diag(H.p, n, n, hd.p, s);
   if (hipMemcpyAsync(dh.data(), hd.p, sizeof(double) * n, hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -820,8 +820,8 @@ int tda_oscillator_strengths(ace_ctx* c, const void* phi_occ, int no, const void
   if (is_cplx(c->dtype)) return ACE_ERR_UNSUPPORTED;
   const int nov = no * nv;
   DevBuf D, dk;
-  int rc = D.alloc((size_t)3 * nov);
-  if (!rc) rc = dk.alloc((size_t)3 * nstates);
+  int rc = D.alloc(c, (size_t)3 * nov);
+  if (!rc) rc = dk.alloc(c, (size_t)3 * nstates);
   if (rc) return rc;
   launch_dipoles(is_fp64(c->dtype), phi_occ, no, phi_virt, nv, c->n, c->h, D.p, c->stream);
   // d_k[c] = sum_ia X_k[ia] D[c][ia]

@@ -85,21 +85,6 @@ inline void free_blob(Blob& b) {
 
 inline int hip_check(hipError_t e) { return e == hipSuccess ? ACE_OK : ACE_ERR_HIP; }
 
-struct DevBuf {
-  double* p = nullptr;
-  ~DevBuf() {
-    if (p) (void)hipFree(p);
-  }
-  int alloc(size_t n) {
-    if (hipMalloc(&p, n * sizeof(double)) != hipSuccess) {
-      (void)hipGetLastError();
-      p = nullptr;
-      return ACE_ERR_OOM;
-    }
-    return ACE_OK;
-  }
-};
-
 }  // namespace host
 }  // namespace ace
 
@@ -169,9 +154,10 @@ struct ace_ctx {
   // ace_build_apply: Gram partials of W^H psi (M's are in `part` at the same time) and the
   // reduced W^H psi dV
   ace::host::Buf part2, ybuf;
-  // Workspace of the SCF pieces (block eigensolver, Hartree and preconditioner scratch): as large
-  // as the largest call so far, used by one call at a time, freed with the context.
+  // Workspace of the SCF pieces (block eigensolver, Hartree and preconditioner scratch), see
+  // ScfUse: kept between calls, used by one at a time.
   ace::host::Buf scf;
+  bool scf_busy = false;
   double* pinned_scf = nullptr;             // landing place of the eigensolver's host values
   ace::host::Blob tda_items;                // pair pointers of the TDA solves
   std::vector<int> pairs_cached;
@@ -187,6 +173,66 @@ struct ace_ctx {
 namespace ace {
 namespace host {
 
+inline int release_scf(ace_ctx* c) {
+  if (hipStreamSynchronize(c->stream) != hipSuccess) return ACE_ERR_HIP;
+  (void)hipFree(c->scf.p);
+  c->scf = Buf();
+  return ACE_OK;
+}
+
+// hipMalloc for context c, which gives up its idle SCF workspace when device memory runs out.
+template <typename T>
+int ctx_malloc(ace_ctx* c, T** p, size_t bytes) {
+  if (hipMalloc(p, bytes) == hipSuccess) return ACE_OK;
+  (void)hipGetLastError();
+  if (c && c->scf.p && !c->scf_busy) {
+    int rc = release_scf(c);
+    if (rc) return rc;
+    if (hipMalloc(p, bytes) == hipSuccess) return ACE_OK;
+    (void)hipGetLastError();
+  }
+  *p = nullptr;
+  return ACE_ERR_OOM;
+}
+
+// One call's use of the context's SCF workspace, from open() to the end of the object.  Kept for
+// the next call: allocating and freeing the eigensolver's 25 buffers, Hartree's scratch and unpinned
+// read-backs took 1.8 of the 4.6 ms of a Hartree potential, an ACE build and three eigensolver steps
+// on 16 orbitals of 64^3.  It is as large as the largest call so far, but at most kScfKeep between
+// calls (as the FFT volumes of a pair solve; the eigensolver's largest, 64 vectors of 64^3 in FP64,
+// takes 0.7 GB), and given up when another allocation of the context fails.
+constexpr size_t kScfKeep = size_t(1) << 30;
+struct ScfUse {
+  ace_ctx* c = nullptr;
+  ScfUse() = default;
+  ScfUse(const ScfUse&) = delete;
+  ScfUse& operator=(const ScfUse&) = delete;
+  ~ScfUse() {
+    if (!c) return;
+    c->scf_busy = false;
+    if (c->scf.cap > kScfKeep) (void)release_scf(c);
+  }
+  int open(ace_ctx* c_, size_t bytes) {
+    c = c_;
+    c->scf_busy = true;
+    if (bytes <= c->scf.cap) return ACE_OK;
+    if (c->scf.p) {
+      int rc = release_scf(c);
+      if (rc) return rc;
+    }
+    int rc = ctx_malloc(c, &c->scf.p, bytes);
+    if (!rc) c->scf.cap = bytes;
+    return rc;
+  }
+};
+
+struct DevBuf {
+  double* p = nullptr;
+  ~DevBuf() {
+    if (p) (void)hipFree(p);
+  }
+  int alloc(ace_ctx* c, size_t n) { return ctx_malloc(c, &p, n * sizeof(double)); }
+};
 
 inline int ensure(ace_ctx* c, Buf& b, size_t bytes) {
   if (bytes <= b.cap) return ACE_OK;
@@ -197,13 +243,9 @@ inline int ensure(ace_ctx* c, Buf& b, size_t bytes) {
     b.cap = 0;
   }
   size_t want = bytes + bytes / 8;
-  if (hipMalloc(&b.p, want) != hipSuccess) {
-    (void)hipGetLastError();
-    b.p = nullptr;
-    return ACE_ERR_OOM;
-  }
-  b.cap = want;
-  return ACE_OK;
+  int rc = ctx_malloc(c, &b.p, want);
+  if (!rc) b.cap = want;
+  return rc;
 }
 
 // Upload a pair list to the context's device pair buffer (skipped if unchanged).

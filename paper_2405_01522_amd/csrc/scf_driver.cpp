@@ -39,14 +39,7 @@ struct Mem {
   ~Mem() {
     if (p) (void)hipFree(p);
   }
-  int alloc(size_t bytes) {
-    if (hipMalloc(&p, std::max<size_t>(bytes, 256)) != hipSuccess) {
-      (void)hipGetLastError();
-      p = nullptr;
-      return ACE_ERR_OOM;
-    }
-    return ACE_OK;
-  }
+  int alloc(ace_ctx* c, size_t bytes) { return ctx_malloc(c, &p, std::max<size_t>(bytes, 256)); }
   double* d() const { return (double*)p; }
   float* f() const { return (float*)p; }
 };
@@ -57,26 +50,6 @@ struct View {
   double* d() const { return (double*)p; }
   float* f() const { return (float*)p; }
 };
-
-// At least `bytes` of the context's SCF workspace.  Allocation and release of the eigensolver's 25
-// buffers, Hartree's scratch and unpinned read-backs took 1.8 of the 4.6 ms of a Hartree potential,
-// an ACE build and three eigensolver steps on 16 orbitals of 64^3.  (Exactly what is asked for, so
-// that a call fits wherever separate buffers would.)
-int scf_workspace(ace_ctx* c, size_t bytes) {
-  if (bytes <= c->scf.cap) return ACE_OK;
-  if (c->scf.p) {
-    if (hipStreamSynchronize(c->stream) != hipSuccess) return ACE_ERR_HIP;
-    (void)hipFree(c->scf.p);
-    c->scf = Buf();
-  }
-  if (hipMalloc(&c->scf.p, bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    c->scf.p = nullptr;
-    return ACE_ERR_OOM;
-  }
-  c->scf.cap = bytes;
-  return ACE_OK;
-}
 
 bool real_ctx(const ace_ctx* c) { return c->dtype == ACE_R64 || c->dtype == ACE_R32; }
 
@@ -101,6 +74,7 @@ struct Eig {
   int kconv = 0;  // the lowest kconv Ritz pairs decide convergence (0: all k)
   double h = 0, dv = 0;
   hipStream_t s = nullptr;
+  ScfUse use;
   View V, HV, V2, HV2, R, tmp, nin, nout;
   View S, G, Ss, Gs, D, ws, U, T, TG, A, th, Y, Cm, Gr, rd, scale, part, zl, cholok;
   const void* lock = nullptr;  // converged vectors the search space is kept orthogonal to
@@ -145,7 +119,7 @@ struct Eig {
     if (nlock) want({&zl}, sizeof(double) * (size_t)nlock * nw * k);
     size_t total = 0;
     for (auto& x : parts) total += x.second;
-    int rc = scf_workspace(c, total);
+    int rc = use.open(c, total);
     if (rc) return rc;
     if (!c->pinned_scf &&
         hipHostMalloc((void**)&c->pinned_scf, 2 * sizeof(double) * kJacobiMax) != hipSuccess) {
@@ -355,7 +329,7 @@ int energies(ace_ctx* c, Eig& e, const void* v_ext, const void* phi, int k, cons
   const bool fp64 = e.fp64;
   hipStream_t s = c->stream;
   Mem sm;
-  int rc = sm.alloc(sizeof(double) * (k * k + 4));
+  int rc = sm.alloc(c, sizeof(double) * (k * k + 4));
   if (rc) return rc;
   double* kin = sm.d();
   double* ex = kin + k * k;
@@ -410,7 +384,8 @@ int scf_density(ace_ctx* c, const void* phi, int k, void* rho) {
 int hartree_potential(ace_ctx* c, const void* rho, void* v_h) {
   if (!c || !rho || !v_h) return ACE_ERR_INVALID;
   if (!real_ctx(c)) return ACE_ERR_UNSUPPORTED;
-  int rc = scf_workspace(c, elem_bytes(c->dtype) * c->ng);
+  ScfUse use;
+  int rc = use.open(c, elem_bytes(c->dtype) * c->ng);
   if (rc) return rc;
   launch_fill(c->dtype == ACE_R64, 1.0, c->ng, c->scf.p, c->stream);
   rc = hartree(c, rho, c->scf.p, v_h);
@@ -423,8 +398,9 @@ int kinetic_precondition(ace_ctx* c, const void* r, int nv, double shift, int sw
   if (!c || !r || !z || nv < 1 || sweeps < 1 || !(omega > 0.0) || !(omega < 2.0))
     return ACE_ERR_INVALID;
   if (!real_ctx(c)) return ACE_ERR_UNSUPPORTED;
+  ScfUse use;
   if (sweeps > 1) {
-    int rc = scf_workspace(c, elem_bytes(c->dtype) * c->ng * nv);
+    int rc = use.open(c, elem_bytes(c->dtype) * c->ng * nv);
     if (rc) return rc;
   }
   launch_precond_kinetic(c->dtype == ACE_R64, r, nv, c->n, c->h, shift, sweeps, omega, z, c->scf.p,
@@ -475,8 +451,8 @@ int unocc_states(ace_ctx* c, const void* v_local, const void* phi_occ, int no, v
   const size_t vb = elem_bytes(c->dtype) * c->ng;
   hipStream_t s = c->stream;
   Mem targets, xi;
-  if (!rc) rc = targets.alloc(vb * nt);
-  if (!rc) rc = xi.alloc(vb * nt);
+  if (!rc) rc = targets.alloc(c, vb * nt);
+  if (!rc) rc = xi.alloc(c, vb * nt);
   if (rc) return rc;
   if (hipMemcpyAsync(targets.p, phi_occ, vb * no, hipMemcpyDeviceToDevice, s) != hipSuccess)
     return ACE_ERR_HIP;
@@ -521,10 +497,10 @@ int scf_energies(ace_ctx* c, const void* v_ext, const void* phi, int k, double* 
   int rc = e.init(c, k, false);
   Mem ones, rho, vh, xi;
   const size_t vb = elem_bytes(c->dtype) * c->ng;
-  if (!rc) rc = ones.alloc(vb);
-  if (!rc) rc = rho.alloc(vb);
-  if (!rc) rc = vh.alloc(vb);
-  if (!rc) rc = xi.alloc(vb * k);
+  if (!rc) rc = ones.alloc(c, vb);
+  if (!rc) rc = rho.alloc(c, vb);
+  if (!rc) rc = vh.alloc(c, vb);
+  if (!rc) rc = xi.alloc(c, vb * k);
   if (rc) return rc;
   launch_fill(e.fp64, 1.0, c->ng, ones.p, c->stream);
   return energies(c, e, v_ext, phi, k, ones.p, rho.p, vh.p, xi.p, energy);
@@ -561,7 +537,7 @@ int scf_run(ace_ctx* c, const void* v_ext, void* phi, int k, const ace_scf_opts*
                   std::make_pair(&rho_out, vb), std::make_pair(&vh, vb),
                   std::make_pair(&vloc, vb), std::make_pair(&ones, vb),
                   std::make_pair(&small, sizeof(double) * (6 * 64 * 64 + kAbsParts + 8))})
-    if (!rc) rc = pr.first->alloc(pr.second);
+    if (!rc) rc = pr.first->alloc(c, pr.second);
   if (rc) return rc;
   double* O = small.d();
   double* Aq = O + 64 * 64;
@@ -672,10 +648,10 @@ int precond_targets(ace_ctx* c, const void* phi, int k, float* tgt, int count) {
   size_t pts;
   const int nblk = gram_blocks(ng, &pts);
   Mem part, z, g, sc;
-  int rc = part.alloc(sizeof(double) * (size_t)nblk * std::max(k, chunk) * chunk);
-  if (!rc) rc = z.alloc(sizeof(double) * (size_t)k * chunk);
-  if (!rc) rc = g.alloc(sizeof(double) * (size_t)chunk * chunk);
-  if (!rc) rc = sc.alloc(sizeof(double) * (size_t)chunk);
+  int rc = part.alloc(c, sizeof(double) * (size_t)nblk * std::max(k, chunk) * chunk);
+  if (!rc) rc = z.alloc(c, sizeof(double) * (size_t)k * chunk);
+  if (!rc) rc = g.alloc(c, sizeof(double) * (size_t)chunk * chunk);
+  if (!rc) rc = sc.alloc(c, sizeof(double) * (size_t)chunk);
   if (rc) return rc;
   const double dv = c->h * c->h * c->h;
   for (int v0 = 0; v0 < count; v0 += chunk) {
