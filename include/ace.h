@@ -219,8 +219,8 @@ int uhf_coupling(ace_ctx* ctx, const void* occ_a, int no_a, const void* virt_a, 
  * persistent launches over a device list of transform planes (largest edge first), and W / M /
  * Cholesky / xi one launch each over all systems.  All work is enqueued on the batch stream, so
  * a call can be captured into a HIP graph once an earlier eager call has sized the workspaces.
- * Launch shapes (XY-pass planes per workgroup for each edge, threads of the z passes) are tuned
- * by timing the candidates on the first eager call for each (dtype, set of box edges); the
+ * Launch shapes (form of the XY pass, its planes and threads per workgroup for each edge, form and
+ * threads of the z passes) are tuned by timing the candidates on the first eager call for each (dtype, set of box edges); the
  * choices are kept for the process and, when the environment variable ACE_TUNE_CACHE names a
  * file, appended to that file and read from it by later processes.  Every shape gives the same
  * bits.
@@ -249,8 +249,10 @@ int ace_batch_set_stream(ace_batch* batch, void* hip_stream);
 int ace_build_batched(ace_batch* batch, const ace_mol* mols, int nmol);
 
 /* The launch shape used by the last ace_build_batched call, as text (host buffer of len
- * bytes): "dtype=<d>,edges=<n>-<n>... xy=<edge>:<planes>,... zf=<threads> zi=<threads>
- * source=tuned|cache|default". */
+ * bytes): "dtype=<d>,edges=<n>-<n>... xy=<edge>:<planes>:<threads>,... mode=<queue|edge>
+ * zf=<threads> zi=<threads> source=tuned|cache|default".  Planes belong to the persistent XY launch
+ * (mode queue, 1024 threads), threads to the one per edge (0: planes worked by halves, with
+ * threads of that form's own); zf or zi 0: that z pass as one launch per edge. */
 int ace_batch_tuning(ace_batch* batch, char* buf, int len);
 
 /*

@@ -44,7 +44,7 @@ struct BatchGrid {
 // Launch shape of the passes for one (dtype, set of edges).
 struct Tune {
   int k[65] = {};   // XY planes per item of the persistent XY launch, by box edge
-  int nt[65] = {};  // threads of the per-edge XY launches, by box edge
+  int nt[65] = {};  // threads of the per-edge XY launches, by box edge (0: the default, 1024)
   int per_edge = 0; // 1: XY as one launch per edge; 0: one persistent launch
   int zf_nt = 512, zi_nt = 512;  // threads of the persistent z passes; 0: one launch per edge
   std::string source = "default";
@@ -63,7 +63,7 @@ const char* cache_path() {
 }
 
 // cache file lines:  <key> xy=<edge>:<planes>:<threads>,... mode=<queue|edge> zf=<nt> zi=<nt>
-// (zf / zi 0: the z pass as one launch per edge)
+// (threads 0: the edge's launches work planes by halves; zf / zi 0: the z pass as one launch per edge)
 void load_cache_locked() {
   if (g_tune_loaded) return;
   g_tune_loaded = true;
@@ -84,7 +84,7 @@ void load_cache_locked() {
     for (char* tok = std::strtok(xy, ","); tok; tok = std::strtok(nullptr, ",")) {
       int n = 0, k = 0, nt = 0;
       if (std::sscanf(tok, "%d:%d:%d", &n, &k, &nt) == 3 && n > 0 && n <= 64 &&
-          (k == 1 || k == 2 || k == 4) && (nt == 512 || nt == 1024)) {
+          (k == 1 || k == 2 || k == 4) && (nt == 512 || nt == 1024 || nt == 0)) {
         t.k[n] = k;
         t.nt[n] = nt;
       }
@@ -95,13 +95,15 @@ void load_cache_locked() {
   std::fclose(f);
 }
 
-std::string tune_line(const std::string& key, const Tune& t, const std::vector<int>& edges) {
+// halves: edges whose launches all work planes by halves
+std::string tune_line(const std::string& key, const Tune& t, const std::vector<int>& edges,
+                      const bool* halves) {
   std::string s = key + " xy=";
   for (size_t i = 0; i < edges.size(); ++i) {
     char b[48];
     const int e = edges[i];
     std::snprintf(b, sizeof(b), "%s%d:%d:%d", i ? "," : "", e, t.k[e] ? t.k[e] : 1,
-                  t.nt[e] ? t.nt[e] : 1024);
+                  halves[e] ? 0 : t.nt[e] ? t.nt[e] : 1024);
     s += b;
   }
   char b[96];
@@ -445,21 +447,33 @@ int ace_build_batched(ace_batch* b, const ace_mol* mols, int nmol) {
   auto dev_xy = [&]() { return dev_z() + zi.size(); };
   auto dev_mols = [&]() { return (const MolArgs*)(dev_xy() + xyi.size()); };
   auto dev_bsys = [&]() { return (const int*)(dev_mols() + ma.size()); };
-  // the XY pass of chunk c: one persistent launch, or one launch per run of jobs of one
-  // (edge, spacing) with the one-system kernel
+  // end of the run of jobs of one (edge, spacing) that starts at g0
+  auto xy_run_end = [&](size_t g0, size_t j1) {
+    size_t g1 = g0;
+    while (g1 < j1 && jobs[g1].edge == jobs[g0].edge && jobs[g1].gpos == jobs[g0].gpos) ++g1;
+    return g1;
+  };
+  // edges whose runs are all worked by halves: no thread count to choose
+  bool halves[65] = {};
+  for (int e : edges) halves[e] = true;
+  for (size_t c = 0; c + 1 < chunk_start.size(); ++c)
+    for (size_t g0 = chunk_start[c], g1; g0 < chunk_start[c + 1]; g0 = g1) {
+      g1 = xy_run_end(g0, chunk_start[c + 1]);
+      if (!xy_edge_by_halves(jobs[g0].edge, fp64, (int)(g1 - g0))) halves[jobs[g0].edge] = false;
+    }
+  // the XY pass of chunk c: one persistent launch, or one launch per such run with the
+  // one-system kernel
   auto xy_pass = [&](const Tune& t, size_t c) -> int {
     const size_t j0 = chunk_start[c], j1 = chunk_start[c + 1];
     if (!t.per_edge)
       return launch_xy_queue(fp64, dev_jobs(), dev_xy() + xy_off[c],
                              (int)(xy_off[c + 1] - xy_off[c]), xy_lds_of(jobs, j0, j1, fp64), s);
-    for (size_t g0 = j0; g0 < j1;) {
-      size_t g1 = g0;
-      while (g1 < j1 && jobs[g1].edge == jobs[g0].edge && jobs[g1].gpos == jobs[g0].gpos) ++g1;
+    for (size_t g0 = j0, g1; g0 < j1; g0 = g1) {
+      g1 = xy_run_end(g0, j1);
       const int e = jobs[g0].edge;
       if (launch_xy_edge(e, fp64, t.nt[e] ? t.nt[e] : 1024, jobs[g0].work, (int)(g1 - g0),
                          jobs[g0].gpos, jobs[g0].tw, s))
         return -1;
-      g0 = g1;
     }
     return 0;
   };
@@ -504,7 +518,8 @@ int ace_build_batched(ace_batch* b, const ace_mol* mols, int nmol) {
 
   if (may_tune) {
     // Tuner.  XY: the persistent launch with K planes per item, edge by edge (largest first);
-    // the per-edge launches with 512 or 1024 threads, edge by edge; each candidate timed over
+    // the per-edge launches with 512 or 1024 threads, edge by edge (where a launch works whole
+    // planes: the one by halves has its own threads); each candidate timed over
     // the whole XY pass of this batch, the faster form kept.  Then the threads of the z
     // passes.  The z-forward pass is re-run before every XY timing (the XY pass works in
     // place).
@@ -543,6 +558,7 @@ int ace_build_batched(ace_batch* b, const ace_mol* mols, int nmol) {
     te.per_edge = 1;
     double best_e = time_xy(te);
     for (auto e = edges.rbegin(); e != edges.rend(); ++e) {
+      if (halves[*e]) continue;
       Tune t = te;
       t.nt[*e] = 512;
       const double ms = time_xy(t);
@@ -572,13 +588,13 @@ int ace_build_batched(ace_batch* b, const ace_mol* mols, int nmol) {
     }
     std::lock_guard<std::mutex> lock(g_tune_mu);
     g_tune[key] = tune;
-    store_cache_locked(tune_line(key, tune, edges));
+    store_cache_locked(tune_line(key, tune, edges, halves));
   } else {
     set_k(tune);
     rc = upload();
     if (rc) return rc;
   }
-  b->last_tuning = tune_line(key, tune, edges) + " source=" + tune.source;
+  b->last_tuning = tune_line(key, tune, edges, halves) + " source=" + tune.source;
 
   ace::Trace* trp = b->tr();
   rc = run_passes(tune, trp);

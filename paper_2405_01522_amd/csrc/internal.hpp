@@ -120,6 +120,8 @@ int launch_zinv_queue(bool fp64, bool real_packed, const QJob* jobs, const QItem
 // kernels' shapes.  -1 if the edge is not compiled for the precision.
 int launch_z_edge(bool forward, int n, bool fp64, bool real_packed, const QJob* jobs, int count,
                   hipStream_t s);
+// Whether launch_xy_edge works count transforms by halves of their planes, whatever nt is.
+bool xy_edge_by_halves(int n, bool fp64, int count);
 // XY pass of count consecutive transforms of one box edge n (their N*N*P work volumes back to
 // back from work) with the one-system kernel at nt threads (512 or 1024), one plane per
 // workgroup.  -1 if the edge is not compiled for the precision.

@@ -256,6 +256,18 @@ static void xy_edge(int nt, void* work, int count, const void* gpos, const void*
     launch_xy<T, N, 1024>(grid, w, g, t, s);
 }
 
+bool xy_edge_by_halves(int n, bool fp64, int count) {
+#define ACE_CASE(NN) \
+  case NN:           \
+    return fp64 ? by_halves<double, NN>(count) : by_halves<float, NN>(count);
+  switch (n) {
+    ACE_SIZES(ACE_CASE)
+    default:
+      return false;
+  }
+#undef ACE_CASE
+}
+
 int launch_xy_edge(int n, bool fp64, int nt, void* work, int count, const void* gpos,
                    const void* tw, hipStream_t s) {
   if (count <= 0) return 0;

@@ -1,6 +1,6 @@
 """The forms of a batch's XY pass, forced through the tuning file that a process reads (one child
 process per form): the persistent launch and one launch per edge, at the edges worked by halves of
-their planes in either, against the oracle and each other.
+their planes in either, against the oracle and each other; and the tuner's report.
 
 Every form gives the same bits.  Bars against the oracle: those of the batch's other tests, 1e-10 in
 FP64, 1e-6 hartree and 2e-5 of xi in FP32."""
@@ -66,15 +66,25 @@ def test_forms_agree(tmp_path):
     keys = {"c128": "dtype=0,edges=40-56-64", "c64": "dtype=1,edges=40-56-64"}
     shape = {"c128": "40:1:1024,56:1:1024,64:1:1024", "c64": "40:2:512,56:1:512,64:1:1024"}
 
-    def lines(mode, zf, zi):
-        return ["%s xy=%s mode=%s zf=%d zi=%d" % (keys[t], shape[t], mode, zf, zi) for t in keys]
+    def lines(mode, zf, zi, xy=shape):
+        return ["%s xy=%s mode=%s zf=%d zi=%d" % (keys[t], xy[t], mode, zf, zi) for t in keys]
 
+    halves = {"c128": "40:1:0,56:1:0,64:1:0", "c64": "40:1:512,56:1:0,64:1:1024"}
     res = {"queue": _run(tmp_path, "queue", lines("queue", 512, 1024)),
-           "edge": _run(tmp_path, "edge", lines("edge", 0, 0))}
+           "edge": _run(tmp_path, "edge", lines("edge", 0, 0)),
+           "edge, threads 0": _run(tmp_path, "edge0", lines("edge", 1024, 512, halves)),
+           "tuned": _run(tmp_path, "tuned", None)}
     for form, r in res.items():
         for name in keys:
             t = str(r[name + "_tuning"])
-            assert "source=cache" in t and "mode=" + form in t, t
+            if form == "tuned":
+                # FP64: 5 transforms at 40 (400 planes), 5 at 56, 3 at 64: all by halves;
+                # FP32: 7 at 56 by halves, one at 64 not (128 planes), 40 never
+                assert "source=tuned" in t
+                assert ("40:1:0,56:1:0,64:1:0" if name == "c128" else "56:1:0,64:1:") in t, t
+                assert name == "c128" or ("64:1:0" not in t and "40:1:0" not in t), t
+            else:
+                assert "source=cache" in t and "mode=" + form.split(",")[0] in t, t
             for key in res["queue"]:
                 if key.startswith(name) and not key.endswith("tuning"):
                     assert np.array_equal(r[key], res["queue"][key]), (form, key)
