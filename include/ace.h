@@ -322,7 +322,9 @@ int strength_function(const double* omega, const double* f, int nstates, double 
  * Small dense FP64 helpers used by the eigensolver drivers (device arrays, row-major):
  *   dense_gemm: C = alpha op(A) op(B) + beta C, op(X) = X (t = 0) or X^T (t = 1), C is M x N;
  *   sym_eig_small: eigenvalues (ascending, w[n]) and eigenvectors (columns of V) of the
- *   symmetric part of A, n <= 64, by parallel-order Jacobi rotations in one workgroup.
+ *   symmetric part of A, n <= 64, by parallel-order Jacobi rotations in one workgroup.  The stop
+ *   test sums squares: largest entries between about 1e-145 and 1e145 (beyond 1e154 nothing is
+ *   rotated).
  */
 int dense_gemm(int ta, int tb, int M, int N, int K, double alpha, const double* A, int lda,
                const double* B, int ldb, double beta, double* C, int ldc, void* hip_stream);

@@ -111,7 +111,8 @@ __device__ __forceinline__ unsigned hi_halves(unsigned a, unsigned b) {
 // 1 -> 8 channels: out[p][c] = act(b[c] + sum_t w[t][c] in[p + d_t]) (* (mask[p][c] > 0)).
 // Four points along x per thread; the 8 weights of a tap are scalar operands (uniform loads), so
 // the 216 FMAs of a point need 27 LDS reads and no weight reads.  64^3 x 16: 55 us, vector
-// instructions in 60 % of the slots (317 a point, 100 of them for staging and addresses); 48 us
+// instructions in 60 % of the slots (317 a point, 100 of them for staging and addresses; the tile's
+// rows of 18 meet bank conflicts in 48 % of the cycles in which LDS is busy, a fifth of all); 48 us
 // with channel-planar stores, which cost the next layer more than the 7 us.
 constexpr int QX = 8, QY = 8, QZ = 16;  // its tile
 template <bool BIAS, bool RELU, bool MASK>

@@ -514,7 +514,9 @@ constexpr bool supported() {
 //   FP64  edge 48 (32) 119 -> 114, edge 40 (32) 86 -> 77, edge 32 (32) 35.0 -> 41;
 //         edges 64 and 56 (18), against x transforms over strips of 8 and 28 columns beside
 //         the N whole rows: 375 -> 177 and 160 -> 141.
-// Vector instructions now issue in 87 % of the slots at edge 64 in FP32 (78 % before).
+// Vector instructions issue in 90 and 87 % of the slots at edges 56 and 64 in FP32 (78 % at 64 in
+// whole planes), but in 37 to 43 % in FP64, where two workgroups of 8 wavefronts per CU (one at 56
+// and 64) do not cover the LDS reads and barriers.
 // 512 threads: 256 and 768 are slower (FP32 edge 64: 346 and 421 us) except FP64 at edge 56,
 // where 768 threads take 14 items of each column in whole rounds (153 -> 141 us).
 template <typename T, int N>

@@ -229,8 +229,9 @@ struct Eig {
 
   // The k lowest Ritz vectors and F times them from m basis vectors, and with keep_p the new
   // search directions (the update's part outside the first k vectors), into V and HV.  True if R
-  // holds the residuals as well: one pass up to kRitzMax vectors; with more, a thread's four sums
-  // no longer fit its registers, and they are formed one after another.
+  // holds the residuals as well: one pass up to kRitzMax vectors.  With more the sums are formed one
+  // after another: a thread's four sums over 24 vectors take 266 registers in FP64, which leaves
+  // one wavefront per SIMD (125 in FP32, not measured).
   bool update(int m, bool keep_p) {
     const int pb = (1 + nw) * k;  // first vector of the P block
     const bool once = k <= kRitzMax;

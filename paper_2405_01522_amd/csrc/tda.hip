@@ -137,12 +137,13 @@ __global__ __launch_bounds__(kThreads) void k_gemm_nt(Op<T> A, int M, Op<T> B, i
 // (64 x 64 each, 4 x 4 MFMA tiles) multiply out of the other.  Loads run a step ahead in registers.
 // Rows are 128 bytes with their 16-byte pieces exchanged by piece ^ (row / 2 % 8): fragment reads
 // and the 8-byte stores meet no bank conflict.
-// 512 x 512 (upper tiles) and 136 x 528 over 64^3 points: 257 and 231 us, against 366 and 358 us
+// 512 x 512 (upper tiles) and 136 x 528 over 64^3 points: 253 and 197 us, against 366 and 358 us
 // with four wavefronts that did all in turn, two workgroups to a CU (rows of 144 bytes: conflicts
-// at the stores) and tiles past the edge worked like others.  With four staging wavefronts 302 us for the
-// first (their chain of load, split and store is then the longest); without the order of
-// workgroups by XCD 9 % more.  (A workgroup per item instead, on short chunks: 12.8 us for 36 x 528
-// over 16^3 points, 320 items of one step; 11.0 us as below.)
+// at the stores) and tiles past the edge worked like others.  With a workgroup per item instead of
+// one per CU that works its items in turn (below) 257 and 231 us, and on short chunks, 36 x 528 over
+// 16^3 points (320 items of one step), 12.8 us against 11.0.  With four staging wavefronts the first
+// took 302 us (their chain of load, split and store is then the longest); without the order of
+// workgroups by XCD 9 % more.
 constexpr int MT = 128, KB = 64;
 constexpr int kStaging = 512, kMfmaThreads = kStaging + 256;
 constexpr int kRowStep = kStaging / 16, kPieces = MT / kRowStep;  // rows of a staging thread
