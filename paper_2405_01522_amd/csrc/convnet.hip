@@ -1044,8 +1044,13 @@ int convnet_create(void* hip_stream, ace_convnet** out) {
     for (float* b : {net->w, net->weff, net->m, net->v, net->grad})
       if (hipMemcpy(b, zero.data(), NPAR * sizeof(float), hipMemcpyHostToDevice) != hipSuccess)
         rc = ACE_ERR_HIP;
-    // zero parameters: every packed form is zero too
-    if (hipMemset(net->pk, 0, sizeof(Packed)) != hipSuccess) rc = ACE_ERR_HIP;
+    // packed on the network's stream and waited for, as by convnet_set_params: a network may be
+    // used on other streams than its own (a memset of the null stream need not have ended by then)
+    if (!rc) {
+      pack(net);
+      if (hipGetLastError() != hipSuccess || hipStreamSynchronize(net->stream) != hipSuccess)
+        rc = ACE_ERR_HIP;
+    }
   }
   if (rc) {
     (void)hipGetLastError();
